@@ -241,3 +241,34 @@ def test_append_random_geometries_bit_exact():
         if dt == 1:
             assert np.array_equal(d_ks.cpu().numpy().view(np.uint32), hks.view(np.uint32)), case
             assert np.array_equal(d_vs.cpu().numpy().view(np.uint32), hvs.view(np.uint32)), case
+
+
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("Hkv,d,P", [(3, 64, 16), (33, 128, 32), (41, 128, 16)])
+def test_append_odd_and_very_wide_tokens(dt, Hkv, d, P):
+    """Tokens that leave lanes of the workgroup idle (192 values) and that are
+    wider than it holds in registers (more than 4,096 values), through every
+    slot of a page with scales that grow: bit-exact against the oracle."""
+    print(f"[case] append dt={dt} Hkv={Hkv} d={d} P={P}", flush=True)
+    start, bt, k, v, ks, vs, kn, vn = _setup(3, Hkv, d, P, dt, P + 2, seed=700 + Hkv + dt,
+                                             spread=2.0)
+    if dt == 1:
+        ks[int(bt[0, 0])] = float("nan")           # an unset scale: the first token replaces it
+    hk, hv = _np_codes(k, dt).copy(), _np_codes(v, dt).copy()
+    hks = None if ks is None else ks.numpy().copy()
+    hvs = None if vs is None else vs.numpy().copy()
+    d_k, d_v, d_bt = k.cuda(), v.cuda(), torch.from_numpy(bt).cuda()
+    d_ks = None if ks is None else ks.cuda()
+    d_vs = None if vs is None else vs.cuda()
+    for s in range(P + 2):
+        lens = (start + s + 1).astype(np.int32)
+        assert oracle.kv_append(_np_codes(kn[s], 0), _np_codes(vn[s], 0), bt, lens, hk, hv,
+                                kv_dtype=dt, page_size=P, k_scales=hks, v_scales=hvs) == 0
+        lib().dora_kv_append(kn[s].cuda(), vn[s].cuda(), d_bt, torch.from_numpy(lens).cuda(),
+                             d_k, d_v, num_kv_heads=Hkv, page_size=P, kv_dtype=dt,
+                             k_scales=d_ks, v_scales=d_vs)
+    assert np.array_equal(_np_codes(d_k.cpu(), dt), hk)
+    assert np.array_equal(_np_codes(d_v.cpu(), dt), hv)
+    if dt == 1:
+        assert np.array_equal(d_ks.cpu().numpy().view(np.uint32), hks.view(np.uint32))
+        assert np.array_equal(d_vs.cpu().numpy().view(np.uint32), hvs.view(np.uint32))
