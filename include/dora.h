@@ -217,8 +217,8 @@ dora_status dora_decode_attn_noalloc(const dora_decode_desc* desc,
  * page_size) under the same page id as the group's first member; a group of
  * one shares nothing.  Any batch is valid input (S_k = 0 where nothing is
  * shared).  Steps, all enqueued on `stream`, no host round trip: a prefix
- * kernel (per group, KV head and chunk of shared pages: finds S_k, stages the
- * pages in LDS once and applies them to every member's query heads); the
+ * kernel (per group, KV head and chunk of shared pages: finds S_k, reads the
+ * pages once and applies them to every member's query heads); the
  * ordinary decode over each member's remaining pages; its combine, which
  * merges cut segments and folds every row with its group's prefix into out. */
 size_t dora_decode_grouped_workspace_bytes(const dora_decode_desc* desc, int32_t group_size);

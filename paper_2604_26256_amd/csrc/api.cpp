@@ -149,14 +149,15 @@ dora_status validate_tables(const dora_decode_desc& d, const int32_t* block_tabl
 // Grouped decode: where each piece lives in the workspace (the decode
 // workspace first).  The shared prefixes are found on the device, so the
 // prefix launch and its partials are sized for the most chunks any group can
-// have: with chunk = clamp(ceil(S * K * Hkv / T), kPrefixMinChunk,
-// kPrefixMaxChunk), T = kPrefixTargetItems, and S <= stride, a (group, KV
-// head) has at most min(ceil(stride / kPrefixMinChunk),
-// max(ceil(T / (K * Hkv)), ceil(stride / kPrefixMaxChunk))) chunks.
+// have: with chunk = clamp(ceil(S / w), kPrefixMinChunk, kPrefixMaxChunk), w =
+// prefix_chunks_wanted, and S <= stride, a (group, KV head) has at most
+// min(ceil(stride / kPrefixMinChunk), max(w, ceil(stride / kPrefixMaxChunk)))
+// chunks.
 struct GroupedLayout {
   WsLayout dec;
   size_t gshared_off, part_o_off, part_ml_off, out32_off, lse_off, seg_rec_off, total;
   int64_t cmax, items;
+  int32_t chunks_wanted;
 };
 
 bool grouped_layout(const dora_decode_desc& d, int32_t group_size, GroupedLayout* L) {
@@ -166,7 +167,8 @@ bool grouped_layout(const dora_decode_desc& d, int32_t group_size, GroupedLayout
   const int64_t kh = n_groups * d.num_kv_heads;
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   const int64_t lo = cdiv(d.block_table_stride, kPrefixMinChunk);
-  int64_t hi = kh > 0 ? cdiv(kPrefixTargetItems, kh) : 1;
+  L->chunks_wanted = prefix_chunks_wanted(kh);
+  int64_t hi = L->chunks_wanted;
   const int64_t big = cdiv(d.block_table_stride, kPrefixMaxChunk);
   hi = hi > big ? hi : big;
   L->cmax = lo < hi ? lo : hi;
@@ -194,7 +196,7 @@ bool grouped_layout(const dora_decode_desc& d, int32_t group_size, GroupedLayout
 // Host-checkable validity of the group arguments.
 dora_status check_groups(const dora_decode_desc& d, int32_t group_size) {
   if (group_size < 1 || d.num_seqs % group_size != 0) return DORA_ERR_INVALID_ARG;
-  if ((int64_t)group_size * (d.num_q_heads / d.num_kv_heads) > 16 * kPrefixMaxWaves)
+  if ((int64_t)group_size * (d.num_q_heads / d.num_kv_heads) > kPrefixMaxColumns)
     return DORA_ERR_UNSUPPORTED;
   return DORA_OK;
 }
@@ -273,7 +275,7 @@ dora_status enqueue_decode(const dora_decode_desc& d, const void* q, const void*
       cp.num_kv_heads = d.num_kv_heads;
       cp.group_size = gp->group_size;
       cp.cmax = gp->cmax;
-      cp.pre_kh = (int64_t)(d.num_seqs / gp->group_size) * d.num_kv_heads;
+      cp.chunks_wanted = gp->chunks_wanted;
       if (launch_combine_grouped(cp, segs, s) != hipSuccess)
         return DORA_ERR_HIP;
     }
@@ -390,6 +392,7 @@ dora_status dora_decode_attn_grouped(const dora_decode_desc* desc, const void* q
   gp.page_size = d.page_size;
   gp.head_dim = d.head_dim;
   gp.cmax = (int32_t)L.cmax;
+  gp.chunks_wanted = L.chunks_wanted;
   gp.page_bytes = (int64_t)d.num_kv_heads * d.page_size * d.head_dim * e;
   gp.scale_log2 = scale * 1.4426950408889634f;
   if (launch_grouped_prefix(gp, (int)L.items, fp8, s) != hipSuccess) return DORA_ERR_HIP;

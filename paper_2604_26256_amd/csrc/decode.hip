@@ -428,7 +428,7 @@ __device__ __forceinline__ void fold_prefix_chunks(const CombineParams& p, int b
   const int64_t bb = (int64_t)p.seq0 + b;  // index in the whole batch
   const int k = (int)(bb / Mg), m = (int)(bb - (int64_t)k * Mg);
   const int64_t item0 = ((int64_t)k * p.num_kv_heads + g) * p.cmax;
-  const int chunk = prefix_chunk_of(Sk, p.pre_kh);
+  const int chunk = prefix_chunk_of(Sk, p.chunks_wanted);
   const int chunks = (Sk + chunk - 1) / chunk;
   for (int c0 = sg; c0 < chunks; c0 += groups * kCombineBatch) {
     float2 ml[kCombineBatch];
@@ -544,14 +544,15 @@ __global__ __launch_bounds__(THREADS) void combine_kernel(CombineParams p) {
 // (loaded with the record, and dropped if the segment was cut).  Either way
 // the chunk partials of the group's shared prefix are folded in as further
 // pieces before the bf16 store.
-__global__ __launch_bounds__(kCombineThreads) void combine_grouped_kernel(CombineParams p) {
-  __shared__ float sM[kCombineThreads], sS[kCombineThreads];
-  __shared__ f32x4 sAcc[kCombineThreads];
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void combine_grouped_kernel(CombineParams p) {
+  __shared__ float sM[THREADS], sS[THREADS];
+  __shared__ f32x4 sAcc[THREADS];
   const int t = threadIdx.x;
   const int G = p.group, D = p.head_dim;
   const int tasks = G * (D / 4);
   const int tasks_r = (tasks + 63) & ~63;
-  const int groups = kCombineThreads / tasks_r;  // >= 2 since tasks <= 512
+  const int groups = THREADS / tasks_r;  // >= 1: the launcher's rule
   const int task = t % tasks_r, sg = t / tasks_r;
   const bool active = task < tasks && sg < groups;
   const int n = active ? task / (D / 4) : 0, d4 = active ? task - n * (D / 4) : 0;
@@ -709,10 +710,18 @@ hipError_t launch_combine(const CombineParams& p, int64_t waves, hipStream_t s) 
   return hipGetLastError();
 }
 
+// 1,024 threads (several piece groups per segment) while the segments are
+// resident in one round (two workgroups per CU); beyond that 256 threads where
+// they hold a segment's tasks, eight workgroups per CU (2,048 segments of 8 query
+// heads: 18.7 -> 9.2 us; 256 segments of 7: 6.6 us with 1,024).
 hipError_t launch_combine_grouped(const CombineParams& p, int64_t grid, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(combine_grouped_kernel, dim3((unsigned)grid), dim3(kCombineThreads), 0, s,
-                     p);
+  const int tasks = p.group * (p.head_dim / 4);
+  if (grid <= 512 || tasks > 256)
+    hipLaunchKernelGGL(combine_grouped_kernel<kCombineThreads>, dim3((unsigned)grid),
+                       dim3(kCombineThreads), 0, s, p);
+  else
+    hipLaunchKernelGGL(combine_grouped_kernel<256>, dim3((unsigned)grid), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

@@ -82,25 +82,30 @@ struct CombineParams {
   const float* pre_o;           // prefix partials, as GroupedParams::part_o
   const float2* pre_ml;
   int32_t num_seqs, seq0, num_kv_heads, group_size, cmax;
-  int64_t pre_kh;               // groups x KV heads of the whole batch
+  int32_t chunks_wanted;        // as GroupedParams::chunks_wanted
 };
 
 // Grouped decode (groups of sequences sharing a prompt's pages).
-constexpr int kPrefixMaxWaves = 8;      // (member, head) columns per group <= 128
+constexpr int kPrefixMaxColumns = 128;  // (member, query head) columns per group
 constexpr int kPrefixMinChunk = 16;     // shared pages per prefix work item, at least ...
 constexpr int kPrefixMaxChunk = 512;    // ... and at most
-constexpr int kPrefixTargetItems = 512; // prefix work items aimed at (2 per CU)
+constexpr int kPrefixTargetItems = 256; // prefix work items aimed at (1 per CU)
 
-// Pages per prefix work item of a group sharing S pages, with kh (group, KV
-// head) pairs in the batch: about kPrefixTargetItems items over all pairs,
-// clamped to [kPrefixMinChunk, kPrefixMaxChunk].  Item (k, g, c) covers pages
-// [c * chunk, min((c + 1) * chunk, S)); its partials sit at item index
+// Chunks wanted per (group, KV head) so that the kh pairs of a batch fill the
+// prefix kernel's resident workgroups (one per CU) once.
+__host__ __device__ inline int prefix_chunks_wanted(int64_t kh) {
+  return kh > 0 && kh < kPrefixTargetItems ? (int)(kPrefixTargetItems / kh) : 1;
+}
+
+// Pages per prefix work item of a group sharing S pages: S over the chunks
+// wanted, clamped to [kPrefixMinChunk, kPrefixMaxChunk].  Item (k, g, c) covers
+// pages [c * chunk, min((c + 1) * chunk, S)); its partials sit at item index
 // (k * Hkv + g) * cmax + c.  The prefix kernel and the folding combine both
 // derive the split from here.
-__host__ __device__ inline int prefix_chunk_of(int S, int64_t kh) {
-  const int64_t want = ((int64_t)S * kh + kPrefixTargetItems - 1) / kPrefixTargetItems;
+__host__ __device__ inline int prefix_chunk_of(int S, int chunks_wanted) {
+  const int want = (S + chunks_wanted - 1) / chunks_wanted;
   return want < kPrefixMinChunk ? kPrefixMinChunk
-                                : (want > kPrefixMaxChunk ? kPrefixMaxChunk : (int)want);
+                                : (want > kPrefixMaxChunk ? kPrefixMaxChunk : want);
 }
 
 struct GroupedParams {
@@ -120,6 +125,7 @@ struct GroupedParams {
   uint16_t* out;
   int32_t num_seqs, num_q_heads, num_kv_heads, group, stride, group_size, page_size, head_dim;
   int32_t cmax;               // prefix items per (group, KV head), at most
+  int32_t chunks_wanted;      // prefix_chunks_wanted of the batch
   int64_t page_bytes;
   float scale_log2;
 };

@@ -8,11 +8,10 @@
 //   prefix   one workgroup per (group, KV head, chunk of the group's shared
 //            pages).  It finds the group's shared prefix S (leading page ids
 //            equal in every member's row, full pages of every member), then
-//            its waves stage the pages' K and V tiles in LDS (double-buffered,
-//            one barrier per step); each computing wave applies them to a tile
-//            of 16 of the group's (member, query head) columns with the decode
-//            kernel's MFMA/online-softmax step, and writes an unnormalised
-//            partial (o, running max, sum) per column.
+//            its waves load the pages' K and V tiles into MFMA operands and
+//            apply them to the group's (member, query head) columns, two tiles
+//            of 16 per wave, and it writes an unnormalised partial (o, running
+//            max, sum) per column.
 //   suffix   the decode kernel over each member's pages past S, writing fp32
 //            rows and their log-sum-exp for the segments it finishes whole;
 //            its combine merges the cut ones and folds every row with the
@@ -25,9 +24,8 @@
 
 namespace dora {
 
-constexpr int kPrefixThreads = 64 * kPrefixMaxWaves;
-constexpr int kStageSets = 2;  // steps in flight per workgroup (register staging)
-constexpr int NCW = 1;         // column tiles per computing wave (2 measured no faster)
+constexpr int kPrefixWaves = 8;
+constexpr int kPrefixThreads = 64 * kPrefixWaves;
 
 // Shared prefix of group k (all threads of the workgroup get it): the number
 // of leading pages that every member holds in full (floor(len / P), at most
@@ -73,44 +71,144 @@ __device__ int shared_prefix(const GroupedParams& p, int k, int enough) {
   if (threadIdx.x == 0) s_min = cap;
   __syncthreads();
   int first = diff && (int)threadIdx.x < cap ? (int)threadIdx.x : cap;  // smallest mismatch
-  for (int jj = threadIdx.x + blockDim.x; jj < cap; jj += blockDim.x) {
+  // (a thread's later entries cannot be a smaller mismatch than its first)
+  for (int jj = threadIdx.x + blockDim.x; jj < first; jj += blockDim.x) {
     const int32_t ld = bt[jj];
     bool d = false;
     for (int m = 1; m < M; ++m) d |= bt[(int64_t)m * stride + jj] != ld;
-    if (d && jj < first) first = jj;
+    if (d) first = jj;
   }
   if (first < cap) atomicMin(&s_min, first);
   __syncthreads();
   return s_min;
 }
 
-// The split of a group's shared pages into work items: prefix_chunk_of.
-__device__ __forceinline__ int prefix_chunk(int S, const GroupedParams& p) {
-  return prefix_chunk_of(S, (int64_t)(p.num_seqs / p.group_size) * p.num_kv_heads);
+// One step of a computing wave: 32 shared tokens (one 32-token page, or two
+// 16-token pages), whatever the page size and dtype.  The registers hold them
+// as the bf16 operands of a 32-token page (PageRegs<D, 32, false>).
+//
+// Raw bytes of a step as the lanes load them: lane (col, grp) reads, for K, the
+// tokens 8 * (col >> 2) + (col & 3) + 4 * t of both sub-tiles t; for V, the
+// tokens 8 * grp .. + 7.  With 16-token pages the lanes with col >= 8 (K) and
+// grp >= 2 (V, scores, scales) are on the second page.
+template <int D, bool FP8>
+using StepRegs = PageRegs<D, 32, FP8>;
+
+template <int D, bool FP8>
+__device__ __forceinline__ PageRegs<D, 32, false> widen(const StepRegs<D, FP8>& r) {
+  if constexpr (!FP8) {
+    return r;
+  } else {
+    PageRegs<D, 32, false> o;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int s = 0; s < D / 64; ++s) {
+        const u32x4 w = r.k[t * (D / 64) + s];
+        o.k[t * (D / 32) + 2 * s] = __builtin_bit_cast(u32x4, fp8x8_to_bf16(w[0], w[1]));
+        o.k[t * (D / 32) + 2 * s + 1] = __builtin_bit_cast(u32x4, fp8x8_to_bf16(w[2], w[3]));
+      }
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i)
+      o.v[i] = __builtin_bit_cast(u32x4, fp8x8_to_bf16(r.v[i][0], r.v[i][1]));
+    return o;
+  }
 }
 
-// One step consumes PAIR consecutive pages as one virtual page of VP = PAIR * P
-// tokens (bf16 16-token pages go in pairs: half the softmax reductions and
-// barriers; fp8 pages keep their own scales, one page per step).  LDS holds a
-// step in the layout of a VP-token page, so the decode's lane operands apply:
-// K [d/8][VP][8] and V [d][VP] for bf16.
+// The step's scores, softmax weights and weighted values for NC tiles of 16
+// columns.  ksc, vsc: score scale and V scale of this lane's tokens; bias: 0,
+// or -inf in lanes whose tokens are past the prefix.
+template <int D, int NC>
+__device__ __forceinline__ void apply_step(const PageRegs<D, 32, false>& r, float ksc, float vsc,
+                                           float bias, const bf16x8 (&q)[NC][D / 32],
+                                           f32x4 (&acc)[NC][D / 16], float (&m_run)[NC],
+                                           float (&l_run)[NC]) {
+  f32x4 sc[NC][2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) sc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        sc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, r.k[t * (D / 32) + ks]), q[c][ks], sc[c][t], 0, 0, 0);
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sc[c][t][i] = __builtin_fmaf(sc[c][t][i], ksc, bias);
+        mx = fmaxf(mx, sc[c][t][i]);
+      }
+    mx = max_xor32(max_xor16(mx));
+    if (__ballot(mx > m_run[c])) {  // some column's running maximum grows: rescale the tile
+      const float m_new = fmaxf(m_run[c], mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run[c] - m_new);
+      m_run[c] = m_new;
+      l_run[c] *= alpha;
+#pragma unroll
+      for (int i = 0; i < D / 16; ++i) acc[c][i] *= alpha;
+    }
+  }
+  bf16x8 pb[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    float psum = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float e = __builtin_amdgcn_exp2f(sc[c][t][i] - m_run[c]);
+        psum += e;
+        pb[c][4 * t + i] = (__bf16)(e * vsc);
+      }
+    l_run[c] += psum;
+  }
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      acc[c][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[i]), pb[c],
+                                                          acc[c][i], 0, 0, 0);
+}
+
+// One workgroup of 8 waves per item (group k, KV head g, chunk c).  The group's
+// (member, query head) columns form CP pairs of 16-column tiles; wave w holds
+// pair w % CP and takes every SP-th step of the chunk, SP = 8 / CP.  A wave
+// loads its step straight into MFMA operand registers (as the decode kernel
+// does; the CP waves of a step share its lines in the caches), so nothing is
+// staged in LDS and no barrier sits between steps, and each pair gives its wave
+// two independent chains of MFMA and softmax.  At the end the SP partial
+// results of each pair are merged through LDS.  More columns per wave would
+// load and convert a step fewer times, but the accumulators of four tiles of
+// head dim 128 do not leave room for the next step's loads at two waves per
+// SIMD, and with eight tiles the registers spill.
+//   What bounds it: long fp8 chunks by the vector instructions of a step (64
+// half-rate conversions and about 170 others per pair, 1,370 cycles, beside 512
+// of MFMA) at two waves per SIMD; short chunks by what surrounds the steps
+// (detection 5 us, page ids 1 us, merge and partials 5 us).  Before (every step
+// staged in LDS between barriers for 8 waves of one tile each): 16 groups of
+// 16, 64 / 8 heads, fp8, 68.6 -> 52.3 us; 4 groups of 16, 28 / 4 heads, bf16,
+// 18.7 us both.  4 waves, 512 items (two workgroups per CU): 53.6 and 19.1 us;
+// 8 waves, 512 items: 60.6 and 20.5 us.  Moving a column's maximum only when a
+// score exceeds it by 2^8 (fewer rescales): 48 and 18.0 us, but it rounds the
+// largest weight of a column, 0.8% more error against 64 bits: not taken.
 template <int D, int P, bool FP8>
-__global__ __launch_bounds__(kPrefixThreads) void prefix_kernel(GroupedParams p) {
-  constexpr int PAIR = (!FP8 && P == 16) ? 2 : 1;
-  constexpr int VP = PAIR * P;
-  typedef PageRegs<D, VP, FP8> R;
-  typedef typename R::vraw_t vraw_t;
+__global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams p) {
+  constexpr int PAIR = 32 / P;  // pages per step
+  constexpr int KSTEPS = D / 32, DBLK = D / 16;
   constexpr int E = FP8 ? 1 : 2;
   constexpr int TILE = P * D * E;  // bytes of one (page, KV head) K tile; V's is the same
-  constexpr int PIECES = 2 * PAIR * TILE / 16;  // 16-byte pieces per step
-  constexpr int PER = (PIECES + kPrefixThreads - 1) / kPrefixThreads;
-  constexpr int per_t = R::NK / R::NT;
-  // V rows in LDS are padded by 16 bytes where the lanes' row-strided reads
-  // would otherwise meet in the same banks.
-  constexpr int VROW = VP * E >= 32 ? VP * E + 16 : VP * E;
-  constexpr int vrow = 16 * VROW;                 // bytes between 16-row blocks of V
-  constexpr int KBYTES = PAIR * TILE;             // K part of a step in LDS
-  __shared__ __align__(16) uint8_t lds[2][KBYTES + D * VROW];
+  constexpr int ROW = D + 4;       // floats per column in the merge buffer (spreads the banks)
+  typedef StepRegs<D, FP8> R;
+  typedef PageRegs<D, 32, false> W;
+  __shared__ __align__(16) float s_o[kPrefixWaves][16][ROW];  // merge: a tile of every wave
+  __shared__ float s_m[kPrefixWaves][32], s_l[kPrefixWaves][32];
   __shared__ int s_pid[kPrefixMaxChunk];
   __shared__ float s_ksc[FP8 ? kPrefixMaxChunk : 1], s_vsc[FP8 ? kPrefixMaxChunk : 1];
 
@@ -122,17 +220,17 @@ __global__ __launch_bounds__(kPrefixThreads) void prefix_kernel(GroupedParams p)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, grp = lane >> 4;
   const int G = p.group, MG = p.group_size * G;
-  // A computing wave takes NCW tiles of 16 (member, query head) columns (each
-  // K and V operand read from LDS then feeds NCW MFMAs).  Waves past the
-  // columns only stage.
-  const bool computes = wave * 16 * NCW < MG;
-  bf16x8 qop[NCW][D / 32];  // issued first: it does not depend on the prefix
+  const int CP = (MG + 31) / 32, SP = kPrefixWaves / CP;
+  const int pr = wave % CP, phase = wave / CP;  // waves with phase >= SP hold nothing
+
+  // Query operands (issued first: they do not depend on the prefix).
+  bf16x8 q[2][KSTEPS];
 #pragma unroll
-  for (int t = 0; t < NCW; ++t) {
-    const int cg = (wave * NCW + t) * 16 + col;  // column among (member, head) pairs
-    const int m = cg < MG ? cg / G : 0, h = cg < MG ? cg - m * G : 0;
+  for (int h = 0; h < 2; ++h) {
+    const int cg = pr * 32 + h * 16 + col;  // column among (member, head) pairs
+    const int m = cg < MG ? cg / G : 0, n = cg < MG ? cg - m * G : 0;
     const int64_t b = (int64_t)k * p.group_size + m;
-    load_q_operand<D, FP8>(qop[t], p.q + (b * p.num_q_heads + (int64_t)g * G + h) * D, cg < MG);
+    load_q_operand<D, FP8>(q[h], p.q + (b * p.num_q_heads + (int64_t)g * G + n) * D, cg < MG);
   }
 
   // The group's shared prefix; the first workgroup of each group publishes it
@@ -143,24 +241,14 @@ __global__ __launch_bounds__(kPrefixThreads) void prefix_kernel(GroupedParams p)
     p.group_shared[k] = S;
     if (p.shared_out) p.shared_out[k] = S;
   }
-  const int chunk = prefix_chunk(S, p);
+  const int chunk = prefix_chunk_of(S, p.chunks_wanted);
   const int j0 = c * chunk;
   if (j0 >= S) return;  // uniform: this chunk is past the group's prefix
-  const int j1 = j0 + chunk < S ? j0 + chunk : S;
+  const int n_pages = (j0 + chunk < S ? j0 + chunk : S) - j0;
   // The item's page ids (and fp8 scales) go to LDS first: a page load that
   // waited on a block-table load would wait on every load issued before it.
-  f32x4 acc[NCW][D / 16];
-  float m_run[NCW], l_run[NCW];
-#pragma unroll
-  for (int t = 0; t < NCW; ++t) {
-#pragma unroll
-    for (int i = 0; i < D / 16; ++i) acc[t][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m_run[t] = -__builtin_inff();
-    l_run[t] = 0.f;
-  }
-
   const int32_t* bt = p.block_table + (int64_t)k * p.group_size * p.stride;  // the leader's row
-  for (int t = threadIdx.x; t < j1 - j0; t += kPrefixThreads) {
+  for (int t = threadIdx.x; t < n_pages; t += kPrefixThreads) {
     const int pid = bt[j0 + t];
     s_pid[t] = pid;
     if constexpr (FP8) {
@@ -169,100 +257,117 @@ __global__ __launch_bounds__(kPrefixThreads) void prefix_kernel(GroupedParams p)
     }
   }
   __syncthreads();
-  const uint32_t koff = (uint32_t)((grp * VP + tile_token<VP>(0, col)) * 16);
-  const uint32_t voff = (uint32_t)(col * VROW + (VP == 16 ? 4 : 8) * grp * E);
 
-  // Piece o of a step: page h = o / (2 TILE / 16) of the step, then its K tile
-  // and V tile in 16-byte pieces.  lds_of maps it into the VP-token layout.
-  auto lds_of = [&](int o) -> int {
-    const int hh = o / (2 * TILE / 16), w = o - hh * (2 * TILE / 16);
-    if (w < TILE / 16) {  // K piece (dx, token) -> (dx, hh * P + token)
-      const int dx = w / P, t = w - dx * P;
-      return (dx * VP + hh * P + t) * 16;
-    }
-    constexpr int RP = P * E / 16 > 0 ? P * E / 16 : 1;  // 16-byte pieces per V row of a page
-    const int v = w - TILE / 16;  // V piece (row, r) -> row of the step, after page hh
-    const int row = v / RP;
-    return KBYTES + row * VROW + hh * P * E + (v - row * RP) * 16;
-  };
+  f32x4 acc[2][DBLK];
+  float m_run[2], l_run[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int i = 0; i < DBLK; ++i) acc[h][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_run[h] = -__builtin_inff();
+    l_run[h] = 0.f;
+  }
+
+  // Per-lane byte offsets inside a (page, KV head) tile.
+  const uint32_t koff = (uint32_t)((grp * P + ((8 * (col >> 2)) & (P - 1)) + (col & 3)) * 16);
+  const uint32_t voff = (uint32_t)((col * P + ((8 * grp) & (P - 1))) * E);
+  const int n_steps = phase < SP ? (n_pages + PAIR - 1) / PAIR : 0;
   // Loads are never skipped, so the compiler's in-order wait counts stay exact
   // (a load under a branch makes it wait for everything): a step past the end
-  // re-reads the last step, a missing second page re-reads the last page, and
-  // pieces past the step (fp8 16-token pages) re-read an earlier piece.  None
-  // of these duplicates reach a score: LDS only takes the real pieces, and the
-  // tokens of a missing page are masked.
-  u32x4 st[kStageSets][PER];
-  const int n_steps = (j1 - j0 + PAIR - 1) / PAIR;
-  auto fetch = [&](u32x4(&dst)[PER], int step) {
-    step = step < n_steps ? step : n_steps - 1;
+  // re-reads the last one, a missing second page the first.  Neither reaches a
+  // score: the step is not applied, the page's lanes are masked.
+  auto fetch = [&](R& r, int u) {
+    const int t0 = (u < n_steps ? u : n_steps - 1) * PAIR;
+    const int t1 = PAIR == 2 && t0 + 1 < n_pages ? t0 + 1 : t0;
+    const int p0 = __builtin_amdgcn_readfirstlane(s_pid[t0]);
+    const int p1 = __builtin_amdgcn_readfirstlane(s_pid[t1]);
+    const int64_t base0 = (int64_t)p0 * p.page_bytes + (int64_t)g * TILE;
+    const int64_t base1 = (int64_t)p1 * p.page_bytes + (int64_t)g * TILE;
+    const uint8_t* kb = p.k_pages + (PAIR == 2 && col >= 8 ? base1 : base0) + koff;
+    const uint8_t* vb = p.v_pages + (PAIR == 2 && grp >= 2 ? base1 : base0) + voff;
+    constexpr int per_t = R::NK / 2;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int o = (threadIdx.x + i * kPrefixThreads) % PIECES;
-      const int hh = o / (2 * TILE / 16), w = (o - hh * (2 * TILE / 16)) * 16;
-      int j = j0 + step * PAIR + hh;
-      j = j < j1 ? j : j1 - 1;
-      const int64_t pid = s_pid[j - j0];
-      const uint8_t* src = (w < TILE ? p.k_pages + w : p.v_pages + (w - TILE)) +
-                           pid * p.page_bytes + (int64_t)g * TILE;
-      dst[i] = *(const u32x4*)src;
-    }
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int s = 0; s < per_t; ++s)
+        r.k[t * per_t + s] = *(const u32x4*)(kb + (4 * s * P + 4 * t) * 16);
+#pragma unroll
+    for (int i = 0; i < DBLK; ++i)
+      r.v[i] = *(const typename R::vraw_t*)(vb + i * 16 * P * E);
   };
-  auto put = [&](const u32x4(&src)[PER], int buf, int step) {
+  auto apply = [&](W r, int u) {
+    float ksc = p.scale_log2, vsc = 1.f, bias = 0.f;
+    if constexpr (PAIR == 2) {
+      if (u * PAIR + 1 >= n_pages) {  // uniform: the last step has one page
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int o = threadIdx.x + i * kPrefixThreads;
-      const int j = j0 + step * PAIR + o / (2 * TILE / 16);
-      if (o < PIECES && j < j1) *(u32x4*)&lds[buf][lds_of(o)] = src[i];
-    }
-  };
-
+        for (int i = 0; i < W::NK; ++i) r.k[i] = col >= 8 ? u32x4{0u, 0u, 0u, 0u} : r.k[i];
 #pragma unroll
-  for (int r = 0; r < kStageSets; ++r) fetch(st[r], r);
-  put(st[0], 0, 0);
-  __syncthreads();
-  for (int base = 0; base < n_steps; base += kStageSets) {
-#pragma unroll
-    for (int r = 0; r < kStageSets; ++r) {
-      const int u = base + r;  // step u sits in LDS buffer u & 1; its register set r is free
-      fetch(st[r], u + kStageSets);
-      if (u < n_steps) {
-        if (computes) {
-          const int buf = u & 1;
-          R pr;
-#pragma unroll
-          for (int t = 0; t < R::NT; ++t)
-#pragma unroll
-            for (int s = 0; s < per_t; ++s)
-              pr.k[t * per_t + s] = *(const u32x4*)&lds[buf][koff + (4 * s * VP + 4 * t) * 16];
-#pragma unroll
-          for (int i = 0; i < D / 16; ++i)
-            pr.v[i] = *(const vraw_t*)&lds[buf][KBYTES + voff + i * vrow];
-          const int jj = j0 + u * PAIR;
-          float ksc = p.scale_log2, vsc = 1.f;
-          if constexpr (FP8) {
-            ksc = s_ksc[jj - j0];
-            vsc = s_vsc[jj - j0];
-          }
-          const int nvalid = (j1 - jj < PAIR ? j1 - jj : PAIR) * P;  // shared pages are full
-          consume_page_tiles<D, VP, FP8, NCW>(pr, nvalid, ksc, vsc, qop, acc, m_run, l_run);
-        }
-        if (u + 1 < n_steps) put(st[(r + 1) % kStageSets], (u + 1) & 1, u + 1);
-        __syncthreads();
+        for (int i = 0; i < DBLK; ++i) r.v[i] = grp >= 2 ? u32x4{0u, 0u, 0u, 0u} : r.v[i];
+        bias = grp >= 2 ? -__builtin_inff() : 0.f;
       }
+    }
+    if constexpr (FP8) {
+      int t = u * PAIR + (PAIR == 2 && grp >= 2 ? 1 : 0);
+      t = t < n_pages ? t : n_pages - 1;
+      ksc = s_ksc[t];
+      vsc = s_vsc[t];
+    }
+    apply_step<D, 2>(r, ksc, vsc, bias, q, acc, m_run, l_run);
+  };
+  if (phase < n_steps) {
+    R ra, rb;
+    int u = phase;
+    fetch(ra, u);
+    while (true) {
+      fetch(rb, u + SP);
+      apply(widen<D, FP8>(ra), u);
+      if ((u += SP) >= n_steps) break;
+      fetch(ra, u + SP);
+      apply(widen<D, FP8>(rb), u);
+      if ((u += SP) >= n_steps) break;
     }
   }
 
+  // Merge of a pair's SP waves: each scales its accumulators to the columns'
+  // common reference, then the sums go through LDS in a fixed order.  Wave
+  // CP * s + pr holds phase s of pair pr.
 #pragma unroll
-  for (int t = 0; t < NCW; ++t) {
-    const float l_tot = sum_xor32(sum_xor16(l_run[t]));
-    const int cg = (wave * NCW + t) * 16 + col;
-    if (cg < MG) {
-      const int64_t slot = ((int64_t)kg * p.cmax + c) * MG + cg;
-      float* po = p.part_o + slot * D + 4 * grp;
-#pragma unroll
-      for (int i = 0; i < D / 16; ++i) *(f32x4*)(po + 16 * i) = acc[t][i];
-      if (grp == 0) p.part_ml[slot] = make_float2(m_run[t], l_tot);
+  for (int h = 0; h < 2; ++h) {
+    const float l = sum_xor32(sum_xor16(l_run[h]));
+    if (grp == 0) {
+      s_m[wave][h * 16 + col] = m_run[h];
+      s_l[wave][h * 16 + col] = l;
     }
+  }
+  __syncthreads();
+  const int64_t slot0 = ((int64_t)kg * p.cmax + c) * MG;
+  if ((int)threadIdx.x < MG) {
+    const int pc = threadIdx.x >> 5, cc = threadIdx.x & 31;
+    float M = s_m[pc][cc], L = 0.f;
+    for (int s = 1; s < SP; ++s) M = fmaxf(M, s_m[CP * s + pc][cc]);
+    for (int s = 0; s < SP; ++s) {
+      const float m = s_m[CP * s + pc][cc];
+      L += s_l[CP * s + pc][cc] * (m == M ? 1.f : __builtin_amdgcn_exp2f(m - M));
+    }
+    p.part_ml[slot0 + threadIdx.x] = make_float2(M, L);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float M = s_m[pr][h * 16 + col];
+    for (int s = 1; s < SP; ++s) M = fmaxf(M, s_m[CP * s + pr][h * 16 + col]);
+    const float f = m_run[h] == M ? 1.f : __builtin_amdgcn_exp2f(m_run[h] - M);
+#pragma unroll
+    for (int i = 0; i < DBLK; ++i)
+      *(f32x4*)&s_o[wave][col][16 * i + 4 * grp] = acc[h][i] * f;
+    __syncthreads();
+    for (int e = threadIdx.x; e < CP * 16 * (D / 4); e += kPrefixThreads) {
+      const int cc = e / (D / 4), d4 = e - cc * (D / 4);  // column cc & 15 of pair cc >> 4
+      const int pc = cc >> 4, cg = pc * 32 + h * 16 + (cc & 15);
+      f32x4 o = *(const f32x4*)&s_o[pc][cc & 15][4 * d4];
+      for (int s = 1; s < SP; ++s) o += *(const f32x4*)&s_o[CP * s + pc][cc & 15][4 * d4];
+      if (cg < MG) *(f32x4*)(p.part_o + (slot0 + cg) * D + 4 * d4) = o;
+    }
+    if (h == 0) __syncthreads();
   }
 }
 

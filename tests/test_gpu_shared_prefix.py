@@ -189,3 +189,41 @@ def test_grouped_random_geometries():
         assert det.tolist() == shared[::M].tolist(), case
         assert max_abs_err(out, oracle_for(b)) <= TOL[dt], case
         assert (out.float() - run_decode(b).float()).abs().max().item() <= TOL[dt], case
+
+
+@pytest.mark.parametrize("dt,P,G,M,Hkv,groups,prompt,inf", [
+    (0, 16, 11, 3, 1, 2, 16 * 7, False),     # 33 columns (two pairs), odd page count
+    (1, 16, 16, 6, 2, 1, 16 * 33, False),    # 96 columns (three pairs; two waves idle), odd
+    (0, 16, 13, 5, 1, 1, 16 * 17, True),     # an infinity in the last, unpaired page
+    (0, 32, 2, 2, 1, 1, 32 * 530, False),    # more pages than threads: a second detection pass
+    (1, 16, 1, 2, 1, 1, 16, False),          # one shared page: most waves have no step
+    (0, 16, 1, 2, 4, 65, 16 * 21, False),    # more (group, head) pairs than items wanted
+    (1, 32, 8, 2, 8, 65, 32 * 3, False),     # 1,040 segments: the 256-thread combine
+    (0, 16, 16, 2, 8, 65, 16 * 3, False),    # the same with 512 tasks: 1,024 threads
+])
+def test_grouped_split_edges(dt, P, G, M, Hkv, groups, prompt, inf):
+    """The edges of how columns are dealt to waves, shared pages to steps and
+    chunks, and segments to combine threads: against the oracle, or, with an
+    infinity among the values, the same finite and non-finite outputs as the
+    plain decode."""
+    print(f"[case] dt={dt} P={P} G={G} M={M} Hkv={Hkv} groups={groups} prompt={prompt}",
+          flush=True)
+    w = wl.Workload("se", groups * M, G * Hkv, Hkv, 128, P, dt, 16384, "lognormal", 60, 1.0, 1,
+                    400)
+    b, shared = wl.make_grpo_batch(w, group_size=M, prompt_range=(prompt, prompt), device="cuda",
+                                   seed_index=60 + G + M)
+    if inf:
+        last = int(b.block_table_h[0, shared[0] - 1])
+        b.v_pages[last, 0, 5, 3] = float("inf")
+    out, det = _grouped(b, M)
+    assert det.tolist() == shared[::M].tolist()
+    plain = run_decode(b).float()
+    if inf:
+        assert torch.isinf(plain[:M, :, 5]).all() and torch.equal(torch.isfinite(out.float()),
+                                                                  torch.isfinite(plain))
+        fine = torch.isfinite(plain)
+        assert (out.float() - plain)[fine].abs().max().item() <= TOL[dt]
+        return
+    seqs = sample_seqs(b.lengths, 8, seed=9)
+    assert max_abs_err(out, oracle_for(b, seqs), seqs) <= TOL[dt]
+    assert (out.float() - plain).abs().max().item() <= TOL[dt]
