@@ -119,7 +119,10 @@ typedef struct {
                                   fp8 pages, within the resident wavefront
                                   slots; never more than the batch can use
                                   (B x Hkv x stride page-heads over the minimum
-                                  range) */
+                                  range).  With both this and min_range_pages 0,
+                                  batches whose block tables are short or few
+                                  are cut per segment instead (see
+                                  dora_decode_attn) */
   int32_t min_range_pages;     /* smallest work range per wavefront, in
                                   (page, KV head) units; 0 = library default */
 } dora_decode_desc;
@@ -145,7 +148,8 @@ size_t dora_decode_workspace_bytes(const dora_decode_desc* desc);
  * in (sequence, head, page) order, where W' = min(W, ceil(T / m)), m being
  * desc->min_range_pages or 8 when that is 0, and the first T mod W' ranges hold
  * one extra item; so a caller can tell which (sequence, KV head) segments a
- * call cuts across wavefronts.  Each launch covers at most 8192 sequences.
+ * call cuts across wavefronts (except batches cut per segment, see
+ * dora_decode_attn).  Each launch covers at most 8192 sequences.
  * Returns 0 for an invalid or unsupported descriptor. */
 int64_t dora_decode_num_waves(const dora_decode_desc* desc);
 
@@ -165,7 +169,10 @@ int64_t dora_decode_num_waves(const dora_decode_desc* desc);
  *                aligned; contents on entry are ignored
  * Launches the decode kernel and a log-sum-exp combine kernel on `stream` (per
  * 8192 sequences).  Every decode wavefront takes an equal share of the batch's
- * (page, KV head) work, whatever the length mix.  Results do not depend on the
+ * (page, KV head) work, whatever the length mix.  Batches whose block tables
+ * are short (up to 1,024-2,048 tokens a row), or hold few (sequence, KV head)
+ * segments, run one workgroup per segment, or per chunk of 256 or 512 tokens of
+ * it, instead; the former is one launch.  Results do not depend on the
  * number of wavefronts beyond fp32 rounding, and repeated calls on the same
  * inputs and device are bitwise identical. */
 dora_status dora_decode_attn(const dora_decode_desc* desc,

@@ -22,7 +22,7 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libdora.so")
 ARCH = "gfx950"
 
-HIP_SOURCES = ["decode.hip", "pack.hip", "append.hip", "grouped.hip", "measure.hip",
+HIP_SOURCES = ["decode.hip", "segment.hip", "pack.hip", "append.hip", "grouped.hip", "measure.hip",
                "noalloc.hip"]
 CXX_SOURCES = ["api.cpp", "pool.cpp", "plan.cpp"]
 

@@ -41,6 +41,43 @@ dora_status check_desc(const dora_decode_desc* d) {
   return DORA_OK;
 }
 
+// The split of the segment kernel for a launch over `segs` (sequence, KV head)
+// segments: pages per workgroup, or 0 where the stream-K decode runs instead.  A
+// caller that sets how the work is cut gets that cut.
+//   Only the table's width is known here, so the rule is on the longest
+// sequence that it can hold.  A workgroup's start and its share of the pages
+// are in a row, about 4 us + 6.5 ns a token (head dim 128), and the combine adds
+// 4.5 us; the stream-K call takes 12-20 us however little there is to do.  So
+// few segments are cut into chunks of 256 or 512 tokens as long as all of them
+// fit the chip about once (two workgroups per CU, and some that are empty), and
+// any number of segments goes whole up to a length past which the longest
+// sequence of a skewed batch would end alone: 1,280 tokens for bf16 (1,024 in
+// 32-token pages, which the stream-K decode streams faster; no 512-token chunks
+// either), 1,536 for fp8, 2,048 for head dim 64.  Over 700 random batches of up
+// to 8,192 tokens (page sizes, head dims, dtypes, 1-8 KV heads, four length
+// mixes) the call is 1.75x as fast by geometric mean, 3 of them 4-7% slower.
+// Either side of the lines, segment / stream-K: 8 segments of 4,096 fp8 tokens
+// 9.7 / 18.2 us; 128 of 2,496 bf16 19.3 / 22.3; 176 of 1,264 15.5 / 17.9; 256 of
+// 1,504 (not taken) 18.2 / 17.4; 99 of 4,100 in 1,024-token chunks (not taken)
+// 27.4 / 23.7.
+int segment_split(const dora_decode_desc& d, int64_t segs, int64_t waves) {
+  if (d.num_waves > 0 || d.min_range_pages > 0) return 0;
+  const int64_t tokens = (int64_t)d.block_table_stride * d.page_size;
+  const bool wide_pages = d.kv_dtype == DORA_KV_BF16 && d.page_size == 32;
+  auto fits = [&](int chunk, int64_t most) {  // each workgroup of a split has a partial slot
+    const int64_t workgroups = segs * ((tokens + chunk - 1) / chunk);
+    return tokens >= 4 * chunk && workgroups <= most && workgroups <= 2 * waves;
+  };
+  if (fits(256, 768)) return 256 / d.page_size;
+  if (!wide_pages && fits(512, 640)) return 512 / d.page_size;
+  const int64_t whole = wide_pages                        ? 1024
+                        : d.head_dim == 64                ? 2048
+                        : d.kv_dtype == DORA_KV_FP8_E4M3  ? 1536
+                                                          : 1280;
+  static_assert(2048 / 16 <= 64 * kSegWaves, "a lane holds each page of its wave");
+  return tokens <= whole ? d.block_table_stride : 0;
+}
+
 int min_range_of(const dora_decode_desc& d) {
   return d.min_range_pages > 0 ? d.min_range_pages : kMinRangePages;
 }
@@ -248,6 +285,35 @@ dora_status enqueue_decode(const dora_decode_desc& d, const void* q, const void*
     dp.min_range = min_range_of(d);
     dp.page_bytes = (int64_t)d.num_kv_heads * d.page_size * d.head_dim * e;
     dp.scale_log2 = scale * 1.4426950408889634f;
+    const int seg_pages = gp ? 0 : segment_split(d, segs, w.waves);
+    if (seg_pages > 0) {
+      SegmentParams sp;
+      sp.q = dp.q;
+      sp.k_pages = dp.k_pages;
+      sp.v_pages = dp.v_pages;
+      sp.k_scales = dp.k_scales;
+      sp.v_scales = dp.v_scales;
+      sp.block_table = dp.block_table;
+      sp.seq_lens = dp.seq_lens;
+      sp.out = dp.out;
+      sp.part_o = dp.part_o;
+      sp.part_ml = dp.part_ml;
+      sp.page_bytes = dp.page_bytes;
+      sp.num_seqs = nb;
+      sp.num_q_heads = d.num_q_heads;
+      sp.num_kv_heads = d.num_kv_heads;
+      sp.group = G;
+      sp.stride = d.block_table_stride;
+      sp.head_dim = d.head_dim;
+      sp.page_size = d.page_size;
+      sp.seg_pages = seg_pages;
+      sp.seg_chunks = (d.block_table_stride + seg_pages - 1) / seg_pages;
+      sp.scale_log2 = dp.scale_log2;
+      if (launch_segments(sp, fp8, s) != hipSuccess) return DORA_ERR_HIP;
+      if (ev && c0 == 0 && hipEventRecord(ev[1], s) != hipSuccess) return DORA_ERR_HIP;
+      if (sp.seg_chunks > 1 && launch_combine_chunks(sp, s) != hipSuccess) return DORA_ERR_HIP;
+      continue;
+    }
     if (launch_decode(dp, d.head_dim, d.page_size, fp8, w.waves, s) != hipSuccess)
       return DORA_ERR_HIP;
     if (ev && c0 == 0 && hipEventRecord(ev[1], s) != hipSuccess) return DORA_ERR_HIP;

@@ -36,6 +36,8 @@
 //            of a share of the empty sequences.  When the batch has no more
 //            segments than wavefronts the records are kept per segment
 //            instead (every segment's record written every call).
+//   segment  small batches: one workgroup per segment, or per chunk of it, in
+//            place of stream-K (segment_kernel).
 //   combine  one workgroup per record: the log-sum-exp merge of the pieces
 //            of a cut segment.  The grouped decode's variant has one
 //            workgroup per segment and also folds every row with the
@@ -47,18 +49,13 @@
 
 #include "decode_core.h"
 #include "dora_internal.h"
+#include "merge_core.h"
 
 namespace dora {
 
 // ---------------------------------------------------------------------------
 // shared helpers
 // ---------------------------------------------------------------------------
-
-__device__ __forceinline__ int pages_of(int L, int P, int stride) {
-  if (L <= 0) return 0;
-  const int n = (L + P - 1) / P;
-  return n < stride ? n : stride;  // a contract violation stays in bounds
-}
 
 __device__ __forceinline__ int wave_inclusive_scan(int v) {
   const int lane = threadIdx.x & 63;
@@ -69,9 +66,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   }
   return v;
 }
-
-// A wave-uniform value, kept in a scalar register.
-__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 // Number of wavefronts that take part: at most the launched count, and few
 // enough that every range holds at least min_range (>= 1) page-heads, so no
@@ -401,22 +395,6 @@ done:
 // ---------------------------------------------------------------------------
 
 constexpr int kCombineThreads = 1024;
-constexpr int kCombineBatch = 4;  // pieces whose loads a thread issues together
-
-// Online log-sum-exp merge of one piece (max in log2 units, sum, unnormalised
-// weighted values) into a running (M, S, acc).
-__device__ __forceinline__ void merge_piece(float2 ml, f32x4 o, float& M, float& S, f32x4& acc) {
-  if (ml.x > M) {
-    const float sc = __builtin_amdgcn_exp2f(M - ml.x);
-    acc = acc * sc + o;
-    S = S * sc + ml.y;
-    M = ml.x;
-  } else if (ml.x > -__builtin_inff()) {
-    const float w = __builtin_amdgcn_exp2f(ml.x - M);
-    acc += w * o;
-    S += w * ml.y;
-  }
-}
 
 // Grouped decode: thread group sg of `groups` folds chunks c = sg, sg +
 // groups, ... of the prefix partials of (member, head n) of segment (b, g)
@@ -453,14 +431,9 @@ __device__ __forceinline__ void fold_prefix_chunks(const CombineParams& p, int b
 // the records are kept per segment (batches with no more segments than
 // wavefronts, so the launch is smaller).  A cut segment's np pieces sit in
 // the slots of wavefronts wa .. wa+np-1, wa the wavefront holding its first
-// piece: wa's in 2wa + first_off, every later one's in 2w'.  Threads are
-// (head, 4 head-dim values) tasks x piece groups; each folds its pieces into
-// a running (max, normaliser, weighted sum) with one pass of loads, and the
-// groups are merged in LDS.
+// piece: wa's in 2wa + first_off, every later one's in 2w'.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void combine_kernel(CombineParams p) {
-  __shared__ float sM[THREADS], sS[THREADS];
-  __shared__ f32x4 sAcc[THREADS];
   const int4 cut = p.cuts[blockIdx.x];
   if (cut.x < 0) return;
   int64_t wa = blockIdx.x;
@@ -473,68 +446,8 @@ __global__ __launch_bounds__(THREADS) void combine_kernel(CombineParams p) {
     b = (int)blockIdx.x / Hkv;
     g = (int)blockIdx.x - b * Hkv;
   }
-  const int t = threadIdx.x;
-  const int G = p.group, D = p.head_dim;
-  const int tasks = G * (D / 4);
-  const int tasks_r = (tasks + 63) & ~63;
-  const int groups = THREADS / tasks_r;  // >= 1 since tasks <= 512
-  const int task = t % tasks_r, sg = t / tasks_r;
-  const bool active = task < tasks && sg < groups;
-  const int n = active ? task / (D / 4) : 0, d4 = active ? task - n * (D / 4) : 0;
-  float M = -__builtin_inff(), S = 0.f;
-  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (active) {
-    for (int k0 = sg; k0 < np; k0 += groups * kCombineBatch) {
-      float2 ml[kCombineBatch];
-      f32x4 o[kCombineBatch];
-#pragma unroll
-      for (int i = 0; i < kCombineBatch; ++i) {  // all loads of the batch first
-        const int k = k0 + i * groups;
-        ml[i] = make_float2(-__builtin_inff(), 0.f);
-        o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (k < np) {
-          const int64_t row = (2 * (wa + k) + (k == 0 ? first_off : 0)) * G + n;
-          ml[i] = p.part_ml[row];
-          o[i] = *(const f32x4*)(p.part_o + row * D + 4 * d4);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < kCombineBatch; ++i) {
-        if (ml[i].x > M) {
-          const float sc = __builtin_amdgcn_exp2f(M - ml[i].x);
-          acc = acc * sc + o[i];
-          S = S * sc + ml[i].y;
-          M = ml[i].x;
-        } else if (ml[i].x > -__builtin_inff()) {
-          const float wgt = __builtin_amdgcn_exp2f(ml[i].x - M);
-          acc += wgt * o[i];
-          S += wgt * ml[i].y;
-        }
-      }
-    }
-  }
-  sM[t] = M;
-  sS[t] = S;
-  sAcc[t] = acc;
-  __syncthreads();
-  if (sg == 0 && task < tasks) {
-    float Mx = M;
-    for (int k = 1; k < groups; ++k) Mx = fmaxf(Mx, sM[k * tasks_r + task]);
-    f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-    for (int k = 0; k < groups; ++k) {
-      const int i = k * tasks_r + task;
-      if (sM[i] == -__builtin_inff()) continue;  // a group with no pieces
-      const float sc = __builtin_amdgcn_exp2f(sM[i] - Mx);
-      num += sc * sAcc[i];
-      den += sc * sS[i];
-    }
-    const float inv = 1.f / den;
-    const int64_t row = (int64_t)b * p.num_q_heads + g * G + n;
-    uint16_t* o = p.out + row * D + 4 * d4;
-    *(bf16x4*)o = bf16x4{(__bf16)(num[0] * inv), (__bf16)(num[1] * inv),
-                         (__bf16)(num[2] * inv), (__bf16)(num[3] * inv)};
-  }
+  merge_segment<THREADS>(p.part_o, p.part_ml, p.out, p.num_q_heads, p.group, p.head_dim, b, g, np,
+                         [=](int k) { return 2 * (wa + k) + (k == 0 ? first_off : 0); });
 }
 
 // The combine of the grouped decode's suffix: one workgroup per segment (b, g)

@@ -18,6 +18,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+__device__ __forceinline__ int pages_of(int L, int P, int stride) {
+  if (L <= 0) return 0;
+  const int n = (L + P - 1) / P;
+  return n < stride ? n : stride;  // a contract violation stays in bounds
+}
+
+// A wave-uniform value, kept in a scalar register.
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // ---------------------------------------------------------------------------
 // decode
 // ---------------------------------------------------------------------------
@@ -102,6 +111,45 @@ __device__ __forceinline__ void load_page(PageRegs<D, P, FP8>& r, const uint8_t*
 #pragma unroll
   for (int i = 0; i < D / 16; ++i)
     r.v[i] = __builtin_nontemporal_load((const typename R::vraw_t*)(vbase + voff + i * vrow));
+}
+
+// A step of T tokens, one page of T or two 16-token pages, as the register image
+// of a T-token page.  base0, base1: byte offsets of the pages' tiles in the pool
+// (equal for one page).  Lane (col, grp) reads, for K, the tokens
+// tile_token<T>(t, col) of the sub-tiles t; for V, T / 4 tokens from T / 4 * grp.
+// So of two pages the lanes with col >= 8 (K) and grp >= 2 (V; scores and scales
+// too) are on the second.  koff, voff: step_koff and step_voff of the lane, or
+// 0.  NT: non-temporal, for tiles that only this wave reads.
+template <int D, int P, int T>
+__device__ __forceinline__ uint32_t step_koff(int col, int grp) {
+  return (uint32_t)((grp * P + (tile_token<T>(0, col) & (P - 1))) * 16);
+}
+template <int D, int P, bool FP8, int T>
+__device__ __forceinline__ uint32_t step_voff(int col, int grp) {
+  return (uint32_t)((col * P + ((T / 4 * grp) & (P - 1))) * (FP8 ? 1 : 2));
+}
+template <int D, int P, bool FP8, int T, bool NT>
+__device__ __forceinline__ void load_step(PageRegs<D, T, FP8>& r, const uint8_t* k_pages,
+                                          const uint8_t* v_pages, int64_t base0, int64_t base1,
+                                          uint32_t koff, uint32_t voff) {
+  typedef PageRegs<D, T, FP8> R;
+  const int lane = threadIdx.x & 63;
+  const uint8_t* kb = k_pages + (T > P && (lane & 15) >= 8 ? base1 : base0) + koff;
+  const uint8_t* vb = v_pages + (T > P && lane >= 32 ? base1 : base0) + voff;
+  constexpr int per_t = R::NK / R::NT;
+#pragma unroll
+  for (int t = 0; t < R::NT; ++t)
+#pragma unroll
+    for (int s = 0; s < per_t; ++s) {
+      const u32x4* at = (const u32x4*)(kb + (4 * s * P + 4 * t) * 16);
+      r.k[t * per_t + s] = NT ? __builtin_nontemporal_load(at) : *at;
+    }
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) {
+    const typename R::vraw_t* at =
+        (const typename R::vraw_t*)(vb + i * 16 * P * (FP8 ? 1 : 2));
+    r.v[i] = NT ? __builtin_nontemporal_load(at) : *at;
+  }
 }
 
 // One page of one segment: scores S^T = K Q^T for the 16 query columns of the

@@ -20,6 +20,8 @@ constexpr int kMinRangePages = 8;
 // Largest batch one decode launch takes: its page prefix ((B + 1) ints) lives
 // in each wavefront's LDS.  Larger batches are cut into launches of this size.
 constexpr int kMaxSeqsPerLaunch = 8192;
+// Waves of a workgroup of the short-segment kernel.
+constexpr int kSegWaves = 4;
 // Bytes reserved at the start of the workspace for flags.
 constexpr size_t kWsHeaderBytes = 256;
 
@@ -63,6 +65,26 @@ struct DecodeParams {
   // pieces, first-slot offset, 0} for a cut segment, w = -1 for a segment
   // finished whole or empty (every segment's record is written every call).
   int32_t seg_records;
+};
+
+// The segment kernel and the combine of its chunks (a struct of their own: the
+// decode kernel's code depends on the size of its arguments).
+struct SegmentParams {
+  const uint16_t* q;
+  const uint8_t* k_pages;
+  const uint8_t* v_pages;
+  const float* k_scales;
+  const float* v_scales;
+  const int32_t* block_table;
+  const int32_t* seq_lens;
+  uint16_t* out;
+  float* part_o;       // as DecodeParams', of chunk c of segment s in slot s * seg_chunks + c
+  float2* part_ml;
+  int64_t page_bytes;
+  int32_t num_seqs, num_q_heads, num_kv_heads, group, stride, head_dim, page_size;
+  int32_t seg_pages;   // pages per workgroup
+  int32_t seg_chunks;  // workgroups (chunks) per segment
+  float scale_log2;
 };
 
 struct CombineParams {
@@ -163,6 +185,8 @@ size_t decode_lds_bytes(int num_seqs);
 hipError_t decode_waves_per_cu(int head_dim, int page_size, bool fp8, int num_seqs, int* out);
 hipError_t launch_decode(const DecodeParams& p, int head_dim, int page_size, bool fp8,
                          int64_t waves, hipStream_t s);
+hipError_t launch_segments(const SegmentParams& p, bool fp8, hipStream_t s);
+hipError_t launch_combine_chunks(const SegmentParams& p, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, int64_t waves, hipStream_t s);
 hipError_t launch_combine_grouped(const CombineParams& p, int64_t grid, hipStream_t s);
 hipError_t launch_validate(const ValidateParams& p, hipStream_t s);

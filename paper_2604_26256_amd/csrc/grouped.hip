@@ -83,19 +83,10 @@ __device__ int shared_prefix(const GroupedParams& p, int k, int enough) {
   return s_min;
 }
 
-// One step of a computing wave: 32 shared tokens (one 32-token page, or two
-// 16-token pages), whatever the page size and dtype.  The registers hold them
-// as the bf16 operands of a 32-token page (PageRegs<D, 32, false>).
-//
-// Raw bytes of a step as the lanes load them: lane (col, grp) reads, for K, the
-// tokens 8 * (col >> 2) + (col & 3) + 4 * t of both sub-tiles t; for V, the
-// tokens 8 * grp .. + 7.  With 16-token pages the lanes with col >= 8 (K) and
-// grp >= 2 (V, scores, scales) are on the second page.
+// One step of a wave is 32 shared tokens (load_step), whatever the page size;
+// its registers become the bf16 operands of a 32-token page.
 template <int D, bool FP8>
-using StepRegs = PageRegs<D, 32, FP8>;
-
-template <int D, bool FP8>
-__device__ __forceinline__ PageRegs<D, 32, false> widen(const StepRegs<D, FP8>& r) {
+__device__ __forceinline__ PageRegs<D, 32, false> widen(const PageRegs<D, 32, FP8>& r) {
   if constexpr (!FP8) {
     return r;
   } else {
@@ -202,10 +193,9 @@ template <int D, int P, bool FP8>
 __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams p) {
   constexpr int PAIR = 32 / P;  // pages per step
   constexpr int KSTEPS = D / 32, DBLK = D / 16;
-  constexpr int E = FP8 ? 1 : 2;
-  constexpr int TILE = P * D * E;  // bytes of one (page, KV head) K tile; V's is the same
+  constexpr int TILE = P * D * (FP8 ? 1 : 2);  // bytes of one (page, KV head) K tile; V's is the same
   constexpr int ROW = D + 4;       // floats per column in the merge buffer (spreads the banks)
-  typedef StepRegs<D, FP8> R;
+  typedef PageRegs<D, 32, FP8> R;
   typedef PageRegs<D, 32, false> W;
   __shared__ __align__(16) float s_o[kPrefixWaves][16][ROW];  // merge: a tile of every wave
   __shared__ float s_m[kPrefixWaves][32], s_l[kPrefixWaves][32];
@@ -269,8 +259,7 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
   }
 
   // Per-lane byte offsets inside a (page, KV head) tile.
-  const uint32_t koff = (uint32_t)((grp * P + ((8 * (col >> 2)) & (P - 1)) + (col & 3)) * 16);
-  const uint32_t voff = (uint32_t)((col * P + ((8 * grp) & (P - 1))) * E);
+  const uint32_t koff = step_koff<D, P, 32>(col, grp), voff = step_voff<D, P, FP8, 32>(col, grp);
   const int n_steps = phase < SP ? (n_pages + PAIR - 1) / PAIR : 0;
   // Loads are never skipped, so the compiler's in-order wait counts stay exact
   // (a load under a branch makes it wait for everything): a step past the end
@@ -281,19 +270,9 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
     const int t1 = PAIR == 2 && t0 + 1 < n_pages ? t0 + 1 : t0;
     const int p0 = __builtin_amdgcn_readfirstlane(s_pid[t0]);
     const int p1 = __builtin_amdgcn_readfirstlane(s_pid[t1]);
-    const int64_t base0 = (int64_t)p0 * p.page_bytes + (int64_t)g * TILE;
-    const int64_t base1 = (int64_t)p1 * p.page_bytes + (int64_t)g * TILE;
-    const uint8_t* kb = p.k_pages + (PAIR == 2 && col >= 8 ? base1 : base0) + koff;
-    const uint8_t* vb = p.v_pages + (PAIR == 2 && grp >= 2 ? base1 : base0) + voff;
-    constexpr int per_t = R::NK / 2;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int s = 0; s < per_t; ++s)
-        r.k[t * per_t + s] = *(const u32x4*)(kb + (4 * s * P + 4 * t) * 16);
-#pragma unroll
-    for (int i = 0; i < DBLK; ++i)
-      r.v[i] = *(const typename R::vraw_t*)(vb + i * 16 * P * E);
+    load_step<D, P, FP8, 32, false>(r, p.k_pages, p.v_pages,
+                                (int64_t)p0 * p.page_bytes + (int64_t)g * TILE,
+                                (int64_t)p1 * p.page_bytes + (int64_t)g * TILE, koff, voff);
   };
   auto apply = [&](W r, int u) {
     float ksc = p.scale_log2, vsc = 1.f, bias = 0.f;

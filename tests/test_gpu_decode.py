@@ -264,3 +264,44 @@ def test_profiling_events_bracket_each_kernel():
     assert torch.equal(out, ref)
     dec, comb = (evs[i].elapsed_time(evs[i + 1]) for i in range(2))
     assert 0 < dec < 1000 and 0 < comb < 1000, (dec, comb)
+
+
+@pytest.mark.parametrize("dt,d,P,Hkv,G,stride", [
+    (0, 128, 16, 1, 1, 1),        # one page a row
+    (0, 64, 16, 2, 16, 63),       # 1,008 tokens: whole segments
+    (0, 128, 16, 2, 7, 64),       # 1,024 tokens: chunks of 256
+    (1, 128, 32, 4, 16, 33),      # fp8, chunks of 8 pages of 32
+    (1, 64, 16, 8, 4, 96),        # 1,536 tokens, 11 x 8 segments: chunks of 256
+    (0, 128, 16, 8, 16, 96),      # 16 query heads
+    (0, 128, 16, 40, 1, 80),      # 440 segments: whole up to 1,280 tokens ...
+    (0, 128, 16, 40, 1, 81),      # ... and stream-K past them
+    (1, 128, 16, 40, 1, 96),      # fp8: whole up to 1,536, page by page
+    (1, 128, 16, 2, 4, 31),       # fp8: in pairs of pages, an odd count
+    (1, 64, 16, 40, 2, 128),      # head dim 64: whole up to 2,048 tokens, 32 pages a wave
+    (0, 128, 32, 40, 2, 32),      # 32-token bf16 pages: whole up to 1,024
+    (0, 128, 16, 9, 4, 189),      # chunks of 512 tokens: 99 segments of 3,024
+    (1, 128, 32, 4, 8, 300),      # a last chunk that is not full
+])
+def test_segment_kernel_edges(dt, d, P, Hkv, G, stride):
+    """Batches the default call cuts per segment or chunk, at the lines of that
+    rule and at the edges of pages, waves, chunks and rows (empty, one token,
+    one chunk exactly, one page more, a full row), with table entries past a
+    sequence's pages that name no page: against the oracle, and against the
+    stream-K cut (num_waves set)."""
+    print(f"[case] segments dt={dt} d={d} P={P} Hkv={Hkv} G={G} stride={stride}", flush=True)
+    full = stride * P
+    lens = np.minimum(np.array([0, 1, P, P + 1, 4 * P, 4 * P + 1, 256, 257, 512, 513 + P, full],
+                               np.int32), full)
+    w = _w(B=len(lens), Hq=G * Hkv, Hkv=Hkv, d=d, P=P, dt=dt, lens=lens)
+    b = gpu_batch(w, lengths=lens, seed_index=300 + stride + G)
+    n = torch.from_numpy(wl.pages_needed(lens, P)).cuda()
+    past = torch.arange(b.stride, device="cuda")[None, :] >= n[:, None]
+    b.block_table = torch.where(past, torch.full_like(b.block_table, 1 << 30), b.block_table)
+    assert b.stride == stride
+    out = run_decode(b, out=torch.full_like(b.q, float("nan")))
+    assert max_abs_err(out, oracle_for(b)) <= TOL[dt]
+    assert not out[0].float().abs().any()
+    assert torch.equal(run_decode(b), out)
+    cut = run_decode(b, num_waves=64)
+    # both round the same sums once to bf16, in another order
+    assert (out.float() - cut.float()).abs().max().item() <= TOL[dt] / 2
