@@ -337,3 +337,56 @@ def test_pack_unpack_random_geometries_bit_exact():
         torch.cuda.synchronize()
         assert status.item() == d.DORA_OK, case
         _assert_pools_equal_oracle(dst_k, dst_v, dst_ks, dst_vs, expected)
+
+
+@pytest.mark.parametrize("dt,Hkv,d,P,n", [
+    (1, 1, 64, 16, 32768),     # one full layer of the grid's pages
+    (1, 1, 64, 16, 32769),     # ... and one page more
+    (1, 9, 64, 16, 37),        # a page of one full chunk and a rest
+    (0, 1, 64, 16, 5),         # a page smaller than a chunk
+    (0, 2, 128, 16, 3),        # exactly one chunk
+    (1, 2, 64, 16, 0),         # no page: the header alone
+])
+def test_pack_unpack_grid_edges(dt, Hkv, d, P, n):
+    """Page counts and page sizes at the edges of the copy's grid: the packed
+    body, scales and every destination page and scale byte for byte."""
+    print(f"[case] grid dt={dt} Hkv={Hkv} d={d} P={P} n={n}", flush=True)
+    D = lib()
+    N = n + 9
+    g = torch.Generator(device="cuda").manual_seed(n + Hkv)
+    X = wl.chunk_elems(dt)
+    e = 2 if dt == 0 else 1
+    pb = Hkv * d * P * e
+
+    def pool():
+        t = torch.randint(0, 256, (N, pb), generator=g, device="cuda", dtype=torch.uint8)
+        return t.view(torch.bfloat16) if dt == 0 else t
+
+    k, v, k2, v2 = (pool() for _ in range(4))
+    ks, vs, ks2, vs2 = (torch.rand(N, generator=g, device="cuda") for _ in range(4))
+    src = torch.randperm(N, generator=g, device="cuda")[:n].to(torch.int32)
+    dst = torch.randperm(N, generator=g, device="cuda")[:n].to(torch.int32)
+    kw = dict(num_kv_heads=Hkv, page_size=P, head_dim=d, kv_dtype=dt, policy_version=2)
+    shape_k, shape_v = (N, Hkv, d // X, P, X), (N, Hkv, d, P)
+    packed = torch.full((256 + 2 * n * pb + (8 * n if dt else 0),), 0xA5, dtype=torch.uint8,
+                        device="cuda")
+    D.dora_kv_page_pack(k.view(shape_k), v.view(shape_v), src, packed, n_seqs=1,
+                        k_scales=ks if dt else None, v_scales=vs if dt else None, **kw)
+    kb, vb, k2b, v2b = (t.view(torch.uint8).view(N, pb) for t in (k, v, k2, v2))
+    want = [kb[src.long()].flatten(), vb[src.long()].flatten()]
+    if dt:
+        want += [ks[src.long()].view(torch.uint8), vs[src.long()].view(torch.uint8)]
+    assert torch.equal(packed[256:], torch.cat(want))
+    assert bytes(packed[:8].cpu().numpy()) == b"DORAKV01"
+    want_k, want_v = k2b.clone(), v2b.clone()
+    want_k[dst.long()], want_v[dst.long()] = kb[src.long()], vb[src.long()]
+    want_ks, want_vs = ks2.clone(), vs2.clone()
+    want_ks[dst.long()], want_vs[dst.long()] = ks[src.long()], vs[src.long()]
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    D.dora_kv_page_unpack(packed, dst, k2.view(shape_k), v2.view(shape_v), src_version=2,
+                          k_scales=ks2 if dt else None, v_scales=vs2 if dt else None,
+                          dev_status=status, **kw)
+    assert int(status.item()) == D.DORA_OK
+    assert torch.equal(k2b, want_k) and torch.equal(v2b, want_v)
+    if dt:
+        assert torch.equal(ks2, want_ks) and torch.equal(vs2, want_vs)
