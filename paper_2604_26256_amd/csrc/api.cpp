@@ -53,20 +53,34 @@ dora_status check_desc(const dora_decode_desc* d) {
 // any number of segments goes whole up to a length past which the longest
 // sequence of a skewed batch would end alone: 1,280 tokens for bf16 (1,024 in
 // 32-token pages, which the stream-K decode streams faster; no 512-token chunks
-// either), 1,536 for fp8, 2,048 for head dim 64.  Over 700 random batches of up
-// to 8,192 tokens (page sizes, head dims, dtypes, 1-8 KV heads, four length
-// mixes) the call is 1.75x as fast by geometric mean, 3 of them 4-7% slower.
-// Either side of the lines, segment / stream-K: 8 segments of 4,096 fp8 tokens
-// 9.7 / 18.2 us; 128 of 2,496 bf16 19.3 / 22.3; 176 of 1,264 15.5 / 17.9; 256 of
-// 1,504 (not taken) 18.2 / 17.4; 99 of 4,100 in 1,024-token chunks (not taken)
-// 27.4 / 23.7.
+// either), 1,536 for fp8, 2,048 for head dim 64.  Past that length chunks, in
+// several rounds of workgroups, compete with a stream-K call whose own costs
+// (every wave's page prefix, its search, the cuts) weigh up to about 50 us: the
+// chunks go on to 1,024 workgroups of 256 tokens and, for fp8, to 1,280 of 512
+// tokens, 2,048 for head dim 64 (2-4 KiB a page and head, for which stream-K
+// pays as much per page as for four times the bytes).
+//   Over 700 random batches of up to 8,192 tokens (page sizes, head dims,
+// dtypes, 1-8 KV heads, four length mixes) the first lines are 1.75x as fast by
+// geometric mean, 3 of them 4-7% slower.  The lines past the whole length: over
+// 737 more batches that they take (up to 9,000 tokens, six mixes) 1.25x (fp8
+// 1.26x, bf16 1.11x); 7 are more than 3% slower, most of them a long sequence among
+// very short ones.  512-token chunks for bf16 too would gain 5-8% up to 896
+// workgroups where the rows are full and lose where they are not (64 sequences
+// of 28 / 4 heads, 320 tokens at the median, 1,500 at most: 17.4 -> 18.2 us).
+//   Either side of the lines, segment / stream-K: 8 segments of 4,096 fp8 tokens
+// 9.7 / 18.2 us; 128 of 2,496 bf16 19.3 / 22.3; 176 of 1,264 15.5 / 17.9.  Times
+// as fast as stream-K, 512-token chunks, by the number of workgroups (the worst
+// of a bin): fp8, head dim 128, 16-token pages, up to 768 1.20 (1.05), 1,280 1.17
+// (0.96), 1,536 1.12 (0.89), 2,048 1.08 (0.88); fp8, head dim 64, 768 1.44
+// (1.31), 2,048 1.31 (0.83); bf16 in 32-token pages 0.95 and less.  1,024-token
+// chunks gain less than these in every bin.
 int segment_split(const dora_decode_desc& d, int64_t segs, int64_t waves) {
   if (d.num_waves > 0 || d.min_range_pages > 0) return 0;
   const int64_t tokens = (int64_t)d.block_table_stride * d.page_size;
   const bool wide_pages = d.kv_dtype == DORA_KV_BF16 && d.page_size == 32;
+  auto workgroups = [&](int chunk) { return segs * ((tokens + chunk - 1) / chunk); };
   auto fits = [&](int chunk, int64_t most) {  // each workgroup of a split has a partial slot
-    const int64_t workgroups = segs * ((tokens + chunk - 1) / chunk);
-    return tokens >= 4 * chunk && workgroups <= most && workgroups <= 2 * waves;
+    return tokens >= 4 * chunk && workgroups(chunk) <= most && workgroups(chunk) <= 2 * waves;
   };
   if (fits(256, 768)) return 256 / d.page_size;
   if (!wide_pages && fits(512, 640)) return 512 / d.page_size;
@@ -75,7 +89,12 @@ int segment_split(const dora_decode_desc& d, int64_t segs, int64_t waves) {
                         : d.kv_dtype == DORA_KV_FP8_E4M3  ? 1536
                                                           : 1280;
   static_assert(2048 / 16 <= 64 * kSegWaves, "a lane holds each page of its wave");
-  return tokens <= whole ? d.block_table_stride : 0;
+  if (tokens <= whole) return d.block_table_stride;
+  if (wide_pages) return 0;
+  if (workgroups(256) <= 1024 && workgroups(256) <= 2 * waves) return 256 / d.page_size;
+  if (d.kv_dtype == DORA_KV_BF16) return 0;
+  const int64_t most = d.head_dim == 64 ? 2048 : 1280;
+  return workgroups(512) <= most && workgroups(512) <= 2 * waves ? 512 / d.page_size : 0;
 }
 
 int min_range_of(const dora_decode_desc& d) {

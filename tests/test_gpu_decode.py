@@ -281,6 +281,11 @@ def test_profiling_events_bracket_each_kernel():
     (0, 128, 32, 40, 2, 32),      # 32-token bf16 pages: whole up to 1,024
     (0, 128, 16, 9, 4, 189),      # chunks of 512 tokens: 99 segments of 3,024
     (1, 128, 32, 4, 8, 300),      # a last chunk that is not full
+    (0, 128, 16, 14, 2, 81),      # past 1,280 tokens: 924 chunks of 256
+    (0, 128, 16, 20, 1, 100),     # ... and stream-K past 1,024 of them
+    (1, 128, 32, 20, 2, 80),      # fp8: 1,100 chunks of 512
+    (1, 64, 16, 30, 1, 130),      # fp8, head dim 64: 1,650 chunks of 512
+    (1, 64, 16, 40, 1, 129),      # ... and stream-K past 2,048 of them
 ])
 def test_segment_kernel_edges(dt, d, P, Hkv, G, stride):
     """Batches the default call cuts per segment or chunk, at the lines of that
