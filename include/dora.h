@@ -227,7 +227,9 @@ dora_status dora_decode_attn_noalloc(const dora_decode_desc* desc,
  * kernel (per group, KV head and chunk of shared pages: finds S_k, reads the
  * pages once and applies them to every member's query heads); the
  * ordinary decode over each member's remaining pages; its combine, which
- * merges cut segments and folds every row with its group's prefix into out. */
+ * merges cut segments and folds every row with its group's prefix into out.
+ * With shared_pages_out NULL, batches that dora_decode_attn cuts per segment
+ * (small ones) run as that call does: it is faster there. */
 size_t dora_decode_grouped_workspace_bytes(const dora_decode_desc* desc, int32_t group_size);
 dora_status dora_decode_attn_grouped(const dora_decode_desc* desc, const void* q,
                                      const void* k_pages, const void* v_pages,

@@ -227,3 +227,29 @@ def test_grouped_split_edges(dt, P, G, M, Hkv, groups, prompt, inf):
     seqs = sample_seqs(b.lengths, 8, seed=9)
     assert max_abs_err(out, oracle_for(b, seqs), seqs) <= TOL[dt]
     assert (out.float() - plain).abs().max().item() <= TOL[dt]
+
+
+@pytest.mark.parametrize("dt,P,d,G,M,Hkv,groups,prompt,plain", [
+    (0, 16, 128, 7, 4, 2, 2, 1500, True),    # chunks of 256 tokens
+    (1, 16, 64, 4, 8, 8, 4, 2000, True),     # fp8, chunks of 512
+    (1, 32, 128, 8, 4, 1, 1, 31, True),      # no full page to share
+    (0, 16, 128, 2, 2, 8, 64, 300, True),    # 1,024 whole segments ...
+    (0, 16, 128, 2, 2, 8, 65, 300, False),   # ... and 1,040
+    (0, 16, 128, 7, 16, 4, 4, 2000, False),  # bf16, too many chunks
+])
+def test_grouped_call_without_counts(dt, P, d, G, M, Hkv, groups, prompt, plain):
+    """Without shared_pages_out a small batch runs as the plain decode (the
+    same bits), any other as with it; both as the oracle."""
+    w = wl.Workload("sp", groups * M, G * Hkv, Hkv, d, P, dt, 16384, "lognormal", 60, 1.0, 1, 400)
+    b, _ = wl.make_grpo_batch(w, group_size=M, prompt_range=(prompt, prompt), device="cuda",
+                              seed_index=90 + G + M)
+    out = torch.full_like(b.q, float("nan"))
+    lib().dora_decode_attn_grouped(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens,
+                                   b.version_ids, out, group_size=M, num_kv_heads=Hkv,
+                                   page_size=P, kv_dtype=dt, k_scales=b.k_scales,
+                                   v_scales=b.v_scales)
+    with_counts, _ = _grouped(b, M)
+    assert torch.equal(out, run_decode(b) if plain else with_counts)
+    seqs = sample_seqs(b.lengths, 8, seed=9)
+    assert max_abs_err(out, oracle_for(b, seqs), seqs) <= TOL[dt]
+    assert (out.float() - with_counts.float()).abs().max().item() <= TOL[dt]
