@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64, 2) void decode_kernel(DecodeParams p) {
   // running state of the current segment
   f32x4 acc[DBLK];
   bf16x8 qop[QSLOT ? 1 : KSTEPS];
-  float m_run = -__builtin_inff(), l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
   int seg_b = 0, seg_g = 0;
   bool seg_whole = false, seg_here = false, first_seg = true;
   int4 cut = make_int4(-1, 0, 0, 0);  // the cut segment whose first piece is here
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64, 2) void decode_kernel(DecodeParams p) {
     seg_g = g;
     seg_whole = whole;
     seg_here = whole;  // the segment's first page is in this range
-    m_run = -__builtin_inff();
+    m_run = kNoMax;
     l_run = 0.f;
 #pragma unroll
     for (int i = 0; i < DBLK; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -269,13 +269,15 @@ __global__ __launch_bounds__(64, 2) void decode_kernel(DecodeParams p) {
     const float l_tot = sum_xor32(sum_xor16(l_run));
     if (col < G) {
       if (seg_whole) {
-        const float inv = 1.f / l_tot;
+        float inv = 1.f / l_tot;
         const int64_t row = (int64_t)seg_b * Hq + seg_g * G + col;
         if constexpr (SUFFIX) {  // normalised fp32 output and its base-2 log-sum-exp
+          const bool none = l_tot == 0.f;  // every score -inf: no weight (kNoMax), not empty
+          inv = none ? 0.f : inv;
 #pragma unroll
           for (int i = 0; i < DBLK; ++i)
             *(f32x4*)(p.out32 + row * D + 4 * grp + 16 * i) = acc[i] * inv;
-          if (grp == 0) p.lse[row] = m_run + __builtin_amdgcn_logf(l_tot);
+          if (grp == 0) p.lse[row] = none ? kNoMax : m_run + __builtin_amdgcn_logf(l_tot);
         } else {
           uint16_t* o = p.out + row * D + 4 * grp;
 #pragma unroll
@@ -504,7 +506,7 @@ __global__ __launch_bounds__(THREADS) void combine_grouped_kernel(CombineParams 
       }
     } else if (sg == 0) {  // finished whole by the decode
       M = lse;
-      S = lse > -__builtin_inff() ? 1.f : 0.f;
+      S = lse > kNoMax ? 1.f : 0.f;
       acc = o32;
     }
     fold_prefix_chunks(p, b, g, n, d4, Sk, sg, groups, M, S, acc);
@@ -525,7 +527,8 @@ __global__ __launch_bounds__(THREADS) void combine_grouped_kernel(CombineParams 
       num += sc * sAcc[i];
       den += sc * sS[i];
     }
-    const float inv = den > 0.f ? 1.f / den : 0.f;  // an empty row with no prefix is zero
+    // an empty row with no prefix is zero; one whose scores are all -inf is NaN
+    const float inv = Mx == -__builtin_inff() ? 0.f : 1.f / den;
     *(bf16x4*)(p.out + row * D + 4 * d4) =
         bf16x4{(__bf16)(num[0] * inv), (__bf16)(num[1] * inv), (__bf16)(num[2] * inv),
                (__bf16)(num[3] * inv)};

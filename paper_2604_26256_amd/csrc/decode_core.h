@@ -31,6 +31,12 @@ __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlan
 // decode
 // ---------------------------------------------------------------------------
 
+// A column's running maximum before its first score.  Finite, so that a first
+// page whose scores are all -inf leaves sum and accumulator 0 (from -inf, the
+// rescale 2^(-inf - -inf) would make them NaN), while it still lies below every
+// finite score: what holds it as its maximum has no weight in a merge.
+constexpr float kNoMax = -3.402823466e38f;
+
 // Butterflies across the 16-lane rows of a wave (each lane with lane ^ 16, or
 // with lane ^ 32) on gfx950's row-swap permutes, VALU operations instead of
 // an LDS-routed shuffle.  A swap of a value with itself returns, in its two

@@ -254,7 +254,7 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
   for (int h = 0; h < 2; ++h) {
 #pragma unroll
     for (int i = 0; i < DBLK; ++i) acc[h][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m_run[h] = -__builtin_inff();
+    m_run[h] = kNoMax;
     l_run[h] = 0.f;
   }
 

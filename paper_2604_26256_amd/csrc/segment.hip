@@ -61,7 +61,7 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void segment_kernel(SegmentParam
   f32x4 acc[DBLK];
 #pragma unroll
   for (int i = 0; i < DBLK; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -__builtin_inff(), l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
   const int steps = (n_steps - wave + kSegWaves - 1) / kSegWaves;  // <= 0: none for this wave
   if (steps > 0) {
     const uint32_t koff = step_koff<D, P, T>(col, grp), voff = step_voff<D, P, FP8, T>(col, grp);

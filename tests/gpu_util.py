@@ -116,3 +116,20 @@ def page_chunks(lengths, page_size, max_pages):
     if cur:
         runs.append(cur)
     return runs
+
+
+def minus_infinity_pages(b, pages):
+    """Makes every score over `pages` -inf, every other score finite: head-dim
+    index 0 of q is positive, and of K it is -inf there (bf16), or, times the
+    page's scale, past the range of fp32 (fp8, the page's other values 0)."""
+    b.q[:, :, 0] = b.q[:, :, 0].float().abs().add(0.5).to(torch.bfloat16)
+    idx = torch.as_tensor(np.asarray(sorted(pages), np.int64), device="cuda")
+    if b.w.kv_dtype == 0:
+        k = b.k_pages[idx]                       # [n][Hkv][d/8][P][8]
+        k[:, :, 0, :, 0] = -float("inf")
+        b.k_pages[idx] = k
+    else:
+        k = torch.zeros_like(b.k_pages[idx].view(torch.uint8))
+        k[:, :, 0, :, 0] = 0xFE                  # -448
+        b.k_pages.view(torch.uint8)[idx] = k
+        b.k_scales[idx] = 3e38

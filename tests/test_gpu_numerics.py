@@ -10,7 +10,8 @@ import torch
 
 import oracle
 import workloads as wl
-from gpu_util import TOL, gpu_batch, max_abs_err, oracle_for, run_decode
+from gpu_util import (TOL, gpu_batch, max_abs_err, minus_infinity_pages, oracle_for,
+                      run_decode)
 
 pytestmark = pytest.mark.gpu
 
@@ -129,3 +130,25 @@ def test_largest_block_table_stride():
     out = run_decode(b)
     err = max_abs_err(out, oracle_for(b))
     assert err <= TOL[0], err
+
+
+@pytest.mark.parametrize("d,P,dt", [(128, 16, 0), (64, 16, 0), (128, 32, 0), (128, 16, 1),
+                                    (64, 32, 1)])
+def test_pages_of_minus_infinity_scores(d, P, dt):
+    """Pages whose scores are all -inf have no weight, wherever they lie: the
+    first page of a sequence, of a wave, of a chunk, a whole chunk, all pages
+    but the last.  Over the segment kernel (1,120 tokens: chunks of 256) and
+    over the stream-K cut, whose ranges start anywhere."""
+    print(f"[case] -inf pages d={d} P={P} dt={dt}", flush=True)
+    n = 1120 // P
+    runs = [(0, 1), (1, 2), (2, 3), (3, 5), (4, 5), (256 // P, 256 // P + 1),
+            (256 // P, 512 // P), (0, 512 // P), (n - 1, n), (0, n - 1), (7, n - 2)]
+    lens = np.full(len(runs), 1120, np.int32)
+    w = wl.Workload("i", len(runs), 8, 2, d, P, dt, 2 * n * len(runs), "uniform", lo=1, hi=1)
+    b = gpu_batch(w, lengths=lens, seed_index=350 + d + P + dt)
+    minus_infinity_pages(b, [int(b.block_table_h[s, j]) for s, (lo, hi) in enumerate(runs)
+                              for j in range(lo, hi)])
+    ref = oracle_for(b)
+    for cut in ({}, {"min_range_pages": 8}, {"num_waves": 50, "min_range_pages": 1}):
+        err = max_abs_err(run_decode(b, **cut), ref)
+        assert err <= TOL[dt], (cut, err)

@@ -7,7 +7,8 @@ import pytest
 import torch
 
 import workloads as wl
-from gpu_util import TOL, lib, max_abs_err, oracle_for, run_decode, sample_seqs
+from gpu_util import (TOL, lib, max_abs_err, minus_infinity_pages, oracle_for, run_decode,
+                      sample_seqs)
 
 pytestmark = pytest.mark.gpu
 
@@ -253,3 +254,29 @@ def test_grouped_call_without_counts(dt, P, d, G, M, Hkv, groups, prompt, plain)
     seqs = sample_seqs(b.lengths, 8, seed=9)
     assert max_abs_err(out, oracle_for(b, seqs), seqs) <= TOL[dt]
     assert (out.float() - with_counts.float()).abs().max().item() <= TOL[dt]
+
+
+@pytest.mark.parametrize("dt,P,d,G,M", [(0, 16, 128, 7, 4), (1, 32, 128, 8, 16), (0, 32, 64, 1, 2)])
+def test_grouped_pages_of_minus_infinity_scores(dt, P, d, G, M):
+    """Pages whose scores are all -inf have no weight, in the shared prompt
+    (each of its first nine pages in turn, and all but one) and as a member's
+    whole suffix; with the counts (prefix kernel) and without."""
+    print(f"[case] grouped -inf pages dt={dt} P={P} d={d} G={G} M={M}", flush=True)
+    groups, n = 11, 24                            # shared pages of each prompt
+    w = wl.Workload("gi", groups * M, G * 2, 2, d, P, dt, 16384, "lognormal", 200, 1.0, 1, 900)
+    b, shared = wl.make_grpo_batch(w, group_size=M, prompt_range=(n * P, n * P), device="cuda",
+                                   seed_index=95 + dt)
+    pages = [int(b.block_table_h[k * M, k]) for k in range(9)]
+    pages += [int(b.block_table_h[9 * M, j]) for j in range(n - 1)]
+    last = 10 * M + 1
+    pages += [int(x) for x in b.block_table_h[last, n:-(-int(b.lengths[last]) // P)]]
+    minus_infinity_pages(b, pages)
+    ref = oracle_for(b)
+    out, det = _grouped(b, M)
+    assert det.tolist() == shared[::M].tolist()
+    assert max_abs_err(out, ref) <= TOL[dt]
+    out = torch.full_like(b.q, float("nan"))
+    lib().dora_decode_attn_grouped(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens,
+                                   b.version_ids, out, group_size=M, num_kv_heads=2, page_size=P,
+                                   kv_dtype=dt, k_scales=b.k_scales, v_scales=b.v_scales)
+    assert max_abs_err(out, ref) <= TOL[dt]
