@@ -459,79 +459,116 @@ __global__ __launch_bounds__(THREADS) void combine_kernel(CombineParams p) {
 // (loaded with the record, and dropped if the segment was cut).  Either way
 // the chunk partials of the group's shared prefix are folded in as further
 // pieces before the bf16 store.
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void combine_grouped_kernel(CombineParams p) {
+//   PARTS = 4, for many segments: workgroups of 256 threads, so that eight are
+// resident per CU.  Their one to four thread groups would walk a long row's
+// hundreds of pieces in rounds of four loads (265 fp8 rows of 380 tokens, one of
+// 33,000, 28 / 4 heads: 95 us a call), so a segment of more than kFewPieces is
+// shared by the workgroups of four segments that lie gridDim.x / 4 apart: each,
+// done with its own, takes a quarter of the segment's tasks with four times the
+// groups (62 us; with 1,024 threads a segment, whatever their number, 62 us too).
+constexpr int kFewPieces = 16;
+template <int THREADS, int PARTS>
+__global__ __launch_bounds__(THREADS, 8) void combine_grouped_kernel(CombineParams p) {
   __shared__ float sM[THREADS], sS[THREADS];
   __shared__ f32x4 sAcc[THREADS];
   const int t = threadIdx.x;
   const int G = p.group, D = p.head_dim;
-  const int tasks = G * (D / 4);
-  const int tasks_r = (tasks + 63) & ~63;
-  const int groups = THREADS / tasks_r;  // >= 1: the launcher's rule
-  const int task = t % tasks_r, sg = t / tasks_r;
-  const bool active = task < tasks && sg < groups;
-  const int n = active ? task / (D / 4) : 0, d4 = active ? task - n * (D / 4) : 0;
-  const int b = (int)blockIdx.x / p.num_kv_heads, g = (int)blockIdx.x - b * p.num_kv_heads;
-  const int64_t row = (int64_t)b * p.num_q_heads + g * G + n;
-  const int4 cut = p.cuts[blockIdx.x];
-  const int Sk = p.group_shared[(p.seq0 + b) / p.group_size];
-  float M = -__builtin_inff(), S = 0.f;
-  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (active) {
-    float lse = -__builtin_inff();
-    f32x4 o32 = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (sg == 0) {
-      lse = p.lse[row];
-      o32 = *(const f32x4*)(p.out32 + row * D + 4 * d4);
-    }
-    if (cut.x >= 0) {  // uniform: a cut segment's pieces
-      const int64_t wa = cut.x;
-      const int np = cut.y, first_off = cut.z;
-      for (int k0 = sg; k0 < np; k0 += groups * kCombineBatch) {
-        float2 ml[kCombineBatch];
-        f32x4 o[kCombineBatch];
+  const int all = G * (D / 4);  // tasks: a head and 4 head-dim values
+  const int segs = p.num_seqs * p.num_kv_heads;
+  const int apart = (int)gridDim.x / PARTS;
+  const int part = (int)blockIdx.x / apart, base = (int)blockIdx.x - part * apart;
+  uint32_t shared = 0;  // bit k: segment base + k * apart is shared by the parts
+  if constexpr (PARTS > 1) {
 #pragma unroll
-        for (int i = 0; i < kCombineBatch; ++i) {  // all loads of the batch first
-          const int k = k0 + i * groups;
-          ml[i] = make_float2(-__builtin_inff(), 0.f);
-          o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-          if (k < np) {
-            const int64_t r = (2 * (wa + k) + (k == 0 ? first_off : 0)) * G + n;
-            ml[i] = p.part_ml[r];
-            o[i] = *(const f32x4*)(p.part_o + r * D + 4 * d4);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < kCombineBatch; ++i) merge_piece(ml[i], o[i], M, S, acc);
-      }
-    } else if (sg == 0) {  // finished whole by the decode
-      M = lse;
-      S = lse > kNoMax ? 1.f : 0.f;
-      acc = o32;
+    for (int k = 0; k < PARTS; ++k) {
+      const int s = base + k * apart;
+      const int4 c = p.cuts[s < segs ? s : 0];
+      shared |= (uint32_t)(s < segs && c.x >= 0 && c.y > kFewPieces) << k;
     }
-    fold_prefix_chunks(p, b, g, n, d4, Sk, sg, groups, M, S, acc);
   }
-  sM[t] = M;
-  sS[t] = S;
-  sAcc[t] = acc;
-  __syncthreads();
-  if (sg == 0 && task < tasks) {
-    float Mx = M;
-    for (int k = 1; k < groups; ++k) Mx = fmaxf(Mx, sM[k * tasks_r + task]);
-    f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-    for (int k = 0; k < groups; ++k) {
-      const int i = k * tasks_r + task;
-      if (sM[i] == -__builtin_inff()) continue;  // a group with no pieces
-      const float sc = __builtin_amdgcn_exp2f(sM[i] - Mx);
-      num += sc * sAcc[i];
-      den += sc * sS[i];
+  int turn = -1;  // the workgroup's own segment, unless it is shared; then each shared one
+  if ((int)blockIdx.x >= segs || (shared >> part & 1u)) {
+    if (shared == 0) return;
+    turn = __builtin_ctz(shared);
+  }
+#pragma unroll 1
+  for (;;) {
+    const int seg = turn < 0 ? (int)blockIdx.x : base + turn * apart;
+    const int task0 = turn < 0 ? 0 : part * ((all + PARTS - 1) / PARTS);
+    const int per = turn < 0 ? all : (all + PARTS - 1) / PARTS;
+    const int tasks = all - task0 < per ? all - task0 : per;  // <= 0: none for this part
+    const int tasks_r = turn < 0 ? (per + 63) & ~63 : (per + 15) & ~15;
+    const int groups = THREADS / tasks_r;  // >= 1: the launcher's rule
+    const int task = t % tasks_r, sg = t / tasks_r;
+    const bool active = task < tasks && sg < groups;
+    const int n = active ? (task0 + task) / (D / 4) : 0;
+    const int d4 = active ? task0 + task - n * (D / 4) : 0;
+    const int b = seg / p.num_kv_heads, g = seg - b * p.num_kv_heads;
+    const int64_t row = (int64_t)b * p.num_q_heads + g * G + n;
+    const int4 cut = p.cuts[seg];
+    const int Sk = p.group_shared[(p.seq0 + b) / p.group_size];
+    float M = -__builtin_inff(), S = 0.f;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (active) {
+      float lse = -__builtin_inff();
+      f32x4 o32 = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (sg == 0) {
+        lse = p.lse[row];
+        o32 = *(const f32x4*)(p.out32 + row * D + 4 * d4);
+      }
+      if (cut.x >= 0) {  // uniform: a cut segment's pieces
+        const int64_t wa = cut.x;
+        const int np = cut.y, first_off = cut.z;
+        for (int k0 = sg; k0 < np; k0 += groups * kCombineBatch) {
+          float2 ml[kCombineBatch];
+          f32x4 o[kCombineBatch];
+#pragma unroll
+          for (int i = 0; i < kCombineBatch; ++i) {  // all loads of the batch first
+            const int k = k0 + i * groups;
+            ml[i] = make_float2(-__builtin_inff(), 0.f);
+            o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (k < np) {
+              const int64_t r = (2 * (wa + k) + (k == 0 ? first_off : 0)) * G + n;
+              ml[i] = p.part_ml[r];
+              o[i] = *(const f32x4*)(p.part_o + r * D + 4 * d4);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < kCombineBatch; ++i) merge_piece(ml[i], o[i], M, S, acc);
+        }
+      } else if (sg == 0) {  // finished whole by the decode
+        M = lse;
+        S = lse > kNoMax ? 1.f : 0.f;
+        acc = o32;
+      }
+      fold_prefix_chunks(p, b, g, n, d4, Sk, sg, groups, M, S, acc);
     }
-    // an empty row with no prefix is zero; one whose scores are all -inf is NaN
-    const float inv = Mx == -__builtin_inff() ? 0.f : 1.f / den;
-    *(bf16x4*)(p.out + row * D + 4 * d4) =
-        bf16x4{(__bf16)(num[0] * inv), (__bf16)(num[1] * inv), (__bf16)(num[2] * inv),
-               (__bf16)(num[3] * inv)};
+    sM[t] = M;
+    sS[t] = S;
+    sAcc[t] = acc;
+    __syncthreads();
+    if (sg == 0 && task < tasks) {
+      float Mx = M;
+      for (int k = 1; k < groups; ++k) Mx = fmaxf(Mx, sM[k * tasks_r + task]);
+      f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
+      float den = 0.f;
+      for (int k = 0; k < groups; ++k) {
+        const int i = k * tasks_r + task;
+        if (sM[i] == -__builtin_inff()) continue;  // a group with no pieces
+        const float sc = __builtin_amdgcn_exp2f(sM[i] - Mx);
+        num += sc * sAcc[i];
+        den += sc * sS[i];
+      }
+      // an empty row with no prefix is zero; one whose scores are all -inf is NaN
+      const float inv = Mx == -__builtin_inff() ? 0.f : 1.f / den;
+      *(bf16x4*)(p.out + row * D + 4 * d4) =
+          bf16x4{(__bf16)(num[0] * inv), (__bf16)(num[1] * inv), (__bf16)(num[2] * inv),
+                 (__bf16)(num[3] * inv)};
+    }
+    shared &= ~0u << (turn + 1);
+    if (shared == 0) break;
+    turn = __builtin_ctz(shared);
+    __syncthreads();  // the shared arrays are free again
   }
 }
 
@@ -628,16 +665,18 @@ hipError_t launch_combine(const CombineParams& p, int64_t waves, hipStream_t s) 
 
 // 1,024 threads (several piece groups per segment) while the segments are
 // resident in one round (two workgroups per CU); beyond that 256 threads where
-// they hold a segment's tasks, eight workgroups per CU (2,048 segments of 8 query
-// heads: 18.7 -> 9.2 us; 256 segments of 7: 6.6 us with 1,024).
-hipError_t launch_combine_grouped(const CombineParams& p, int64_t grid, hipStream_t s) {
-  if (grid <= 0) return hipSuccess;
-  const int tasks = p.group * (p.head_dim / 4);
-  if (grid <= 512 || tasks > 256)
-    hipLaunchKernelGGL(combine_grouped_kernel<kCombineThreads>, dim3((unsigned)grid),
+// they hold a segment's tasks (16 groups of 16 fp8 sequences, 64 / 8 heads, 2,048
+// segments: 129.6 us a call with 1,024 threads, 122.8 with 256; 640 bf16 segments
+// 58.0 and 55.8; with one long row among short ones, 576 to 912 segments, 1-2 us
+// more than with 1,024, beyond level).
+hipError_t launch_combine_grouped(const CombineParams& p, int64_t segs, hipStream_t s) {
+  if (segs <= 0) return hipSuccess;
+  if (segs <= 512 || p.group * (p.head_dim / 4) > 256)
+    hipLaunchKernelGGL((combine_grouped_kernel<kCombineThreads, 1>), dim3((unsigned)segs),
                        dim3(kCombineThreads), 0, s, p);
   else
-    hipLaunchKernelGGL(combine_grouped_kernel<256>, dim3((unsigned)grid), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((combine_grouped_kernel<256, 4>), dim3((unsigned)((segs + 3) / 4 * 4)),
+                       dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

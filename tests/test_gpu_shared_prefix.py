@@ -280,3 +280,27 @@ def test_grouped_pages_of_minus_infinity_scores(dt, P, d, G, M):
                                    b.version_ids, out, group_size=M, num_kv_heads=2, page_size=P,
                                    kv_dtype=dt, k_scales=b.k_scales, v_scales=b.v_scales)
     assert max_abs_err(out, ref) <= TOL[dt]
+
+
+@pytest.mark.parametrize("dt,P,d,G,Hkv", [(0, 16, 64, 4, 3), (1, 32, 128, 8, 3), (0, 16, 128, 16, 3)])
+def test_grouped_combine_of_many_segments(dt, P, d, G, Hkv):
+    """522 segments (each merged by a workgroup of 256 threads, 16 query heads of
+    128: of 1,024), most in one piece or few, some in up to hundreds (shared by
+    four workgroups; rows 0 and 87 by the same four), some empty."""
+    print(f"[case] many segments dt={dt} P={P} d={d} G={G}", flush=True)
+    lens = np.random.default_rng(6).integers(1, 60, 174).astype(np.int32) + 7 * P
+    lens[[0, 87, 90]] = 16000, 9000, 5000
+    lens[40:80] = 12 * P * np.arange(1, 41)       # every small number of pieces
+    lens[[6, 173]] = 0
+    pages = int(wl.pages_needed(lens, P).sum()) + 8
+    w = wl.Workload("ms", len(lens), G * Hkv, Hkv, d, P, dt, pages, "uniform", lo=1, hi=1)
+    b = wl.make_batch(w, device="cuda", seed_index=96 + dt, lengths=lens)
+    bt = b.block_table_h.copy()
+    bt[1::2, :7] = bt[::2, :7]                    # pairs, 7 pages shared
+    bt[173], bt[7] = b.block_table_h[173], b.block_table_h[7]
+    _set_tables(b, bt)
+    out, det = _grouped(b, 2)
+    assert det.tolist() == [0 if k in (3, 86) else 7 for k in range(87)]
+    seqs = [0, 1, 2, 3, 6, 7, 86, 87, 88, 90, 91, 120, 172, 173]
+    assert max_abs_err(out, oracle_for(b, seqs), seqs) <= TOL[dt]
+    assert (out.float() - run_decode(b).float()).abs().max().item() <= TOL[dt]
