@@ -111,12 +111,17 @@ struct CombineParams {
 constexpr int kPrefixMaxColumns = 128;  // (member, query head) columns per group
 constexpr int kPrefixMinChunk = 16;     // shared pages per prefix work item, at least ...
 constexpr int kPrefixMaxChunk = 512;    // ... and at most
-constexpr int kPrefixTargetItems = 256; // prefix work items aimed at (1 per CU)
+
+// Waves of a prefix workgroup for kh (group, KV head) pairs: 8, one workgroup
+// resident per CU, or, where the pairs leave less than two chunks to each of them,
+// 4 and two workgroups per CU (the figures are at the prefix kernel).
+__host__ __device__ inline int prefix_waves(int64_t kh) { return kh <= 128 ? 8 : 4; }
 
 // Chunks wanted per (group, KV head) so that the kh pairs of a batch fill the
-// prefix kernel's resident workgroups (one per CU) once.
+// prefix kernel's resident workgroups (256 CUs) once.
 __host__ __device__ inline int prefix_chunks_wanted(int64_t kh) {
-  return kh > 0 && kh < kPrefixTargetItems ? (int)(kPrefixTargetItems / kh) : 1;
+  const int items = prefix_waves(kh) == 8 ? 256 : 512;
+  return kh > 0 && kh < items ? (int)(items / kh) : 1;
 }
 
 // Pages per prefix work item of a group sharing S pages: S over the chunks

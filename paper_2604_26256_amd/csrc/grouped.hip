@@ -24,8 +24,8 @@
 
 namespace dora {
 
-constexpr int kPrefixWaves = 8;
-constexpr int kPrefixThreads = 64 * kPrefixWaves;
+// Steps of an item whose waves are not worth a merge (see prefix_kernel).
+constexpr int kAloneSteps = 4;
 
 // Shared prefix of group k (all threads of the workgroup get it): the number
 // of leading pages that every member holds in full (floor(len / P), at most
@@ -168,9 +168,9 @@ __device__ __forceinline__ void apply_step(const PageRegs<D, 32, false>& r, floa
                                                           acc[c][i], 0, 0, 0);
 }
 
-// One workgroup of 8 waves per item (group k, KV head g, chunk c).  The group's
+// One workgroup of WAVES waves per item (group k, KV head g, chunk c).  The group's
 // (member, query head) columns form CP pairs of 16-column tiles; wave w holds
-// pair w % CP and takes every SP-th step of the chunk, SP = 8 / CP.  A wave
+// pair w % CP and takes every SP-th step of the chunk, SP = WAVES / CP.  A wave
 // loads its step straight into MFMA operand registers (as the decode kernel
 // does; the CP waves of a step share its lines in the caches), so nothing is
 // staged in LDS and no barrier sits between steps, and each pair gives its wave
@@ -185,20 +185,31 @@ __device__ __forceinline__ void apply_step(const PageRegs<D, 32, false>& r, floa
 // (detection 5 us, page ids 1 us, merge and partials 5 us).  Before (every step
 // staged in LDS between barriers for 8 waves of one tile each): 16 groups of
 // 16, 64 / 8 heads, fp8, 68.6 -> 52.3 us; 4 groups of 16, 28 / 4 heads, bf16,
-// 18.7 us both.  4 waves, 512 items (two workgroups per CU): 53.6 and 19.1 us;
-// 8 waves, 512 items: 60.6 and 20.5 us.  Moving a column's maximum only when a
-// score exceeds it by 2^8 (fewer rescales): 48 and 18.0 us, but it rounds the
-// largest weight of a column, 0.8% more error against 64 bits: not taken.
-template <int D, int P, bool FP8>
-__global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams p) {
+// 18.7 us both.  Moving a column's maximum only when a score exceeds it by 2^8
+// (fewer rescales): 48 and 18.0 us, but it rounds the largest weight of a column,
+// 0.8% more error against 64 bits: not taken.
+//   An item of at most kAloneSteps steps has no merge: one wave takes all steps
+// of a pair, or of one tile of a pair while there are waves for it (CP <= 2), and
+// writes its partial from registers; the others leave.  Whole calls, 4 groups of
+// 4, 28 / 4 heads, bf16, prompts of 32 / 64 / 128 tokens: 22.8 / 23.0 / 23.4 us
+// with the merge, 19.4 / 20.1 / 21.2 without (8 steps: 24.2 / 25.4).
+//   Waves (prefix_waves): 8, and one item per CU, up to 128 (group, KV head) pairs;
+// beyond, where pairs times whole chunks would leave CUs idle or take two rounds,
+// 4, and two items per CU: 212 pairs (53 groups of 5, 28 / 4 heads, fp8, prompts of
+// 350 tokens) 62.9 -> 57.1 us a call, 472 pairs (59 groups of 2, 128 / 8 heads, fp8)
+// with prompts of 32 / 256 / 3,000 tokens 38.2 / 47.8 / 116 -> 33.5 / 39.0 / 108.
+// Up to 128 pairs 4 waves lose: the prefix kernels of the two batches above take
+// 53.6 and 19.1 us.
+template <int D, int P, bool FP8, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void prefix_kernel(GroupedParams p) {
   constexpr int PAIR = 32 / P;  // pages per step
   constexpr int KSTEPS = D / 32, DBLK = D / 16;
   constexpr int TILE = P * D * (FP8 ? 1 : 2);  // bytes of one (page, KV head) K tile; V's is the same
   constexpr int ROW = D + 4;       // floats per column in the merge buffer (spreads the banks)
   typedef PageRegs<D, 32, FP8> R;
   typedef PageRegs<D, 32, false> W;
-  __shared__ __align__(16) float s_o[kPrefixWaves][16][ROW];  // merge: a tile of every wave
-  __shared__ float s_m[kPrefixWaves][32], s_l[kPrefixWaves][32];
+  __shared__ __align__(16) float s_o[WAVES][16][ROW];  // merge: a tile of every wave
+  __shared__ float s_m[WAVES][32], s_l[WAVES][32];
   __shared__ int s_pid[kPrefixMaxChunk];
   __shared__ float s_ksc[FP8 ? kPrefixMaxChunk : 1], s_vsc[FP8 ? kPrefixMaxChunk : 1];
 
@@ -210,7 +221,7 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, grp = lane >> 4;
   const int G = p.group, MG = p.group_size * G;
-  const int CP = (MG + 31) / 32, SP = kPrefixWaves / CP;
+  const int CP = (MG + 31) / 32, SP = WAVES / CP;
   const int pr = wave % CP, phase = wave / CP;  // waves with phase >= SP hold nothing
 
   // Query operands (issued first: they do not depend on the prefix).
@@ -238,7 +249,7 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
   // The item's page ids (and fp8 scales) go to LDS first: a page load that
   // waited on a block-table load would wait on every load issued before it.
   const int32_t* bt = p.block_table + (int64_t)k * p.group_size * p.stride;  // the leader's row
-  for (int t = threadIdx.x; t < n_pages; t += kPrefixThreads) {
+  for (int t = threadIdx.x; t < n_pages; t += 64 * WAVES) {
     const int pid = bt[j0 + t];
     s_pid[t] = pid;
     if constexpr (FP8) {
@@ -248,19 +259,9 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
   }
   __syncthreads();
 
-  f32x4 acc[2][DBLK];
-  float m_run[2], l_run[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-#pragma unroll
-    for (int i = 0; i < DBLK; ++i) acc[h][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m_run[h] = kNoMax;
-    l_run[h] = 0.f;
-  }
-
   // Per-lane byte offsets inside a (page, KV head) tile.
   const uint32_t koff = step_koff<D, P, 32>(col, grp), voff = step_voff<D, P, FP8, 32>(col, grp);
-  const int n_steps = phase < SP ? (n_pages + PAIR - 1) / PAIR : 0;
+  const int n_steps = (n_pages + PAIR - 1) / PAIR;
   // Loads are never skipped, so the compiler's in-order wait counts stay exact
   // (a load under a branch makes it wait for everything): a step past the end
   // re-reads the last one, a missing second page the first.  Neither reaches a
@@ -274,37 +275,81 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
                                 (int64_t)p0 * p.page_bytes + (int64_t)g * TILE,
                                 (int64_t)p1 * p.page_bytes + (int64_t)g * TILE, koff, voff);
   };
-  auto apply = [&](W r, int u) {
-    float ksc = p.scale_log2, vsc = 1.f, bias = 0.f;
-    if constexpr (PAIR == 2) {
-      if (u * PAIR + 1 >= n_pages) {  // uniform: the last step has one page
+  // Steps first, first + by, ... (first < n_steps) over the NC column tiles of q.
+  auto stream = [&](int first, int by, const auto& q, auto& acc, auto& m_run, auto& l_run) {
+    constexpr int NC = sizeof(m_run) / sizeof(float);
+    auto apply = [&](W r, int u) {
+      float ksc = p.scale_log2, vsc = 1.f, bias = 0.f;
+      if constexpr (PAIR == 2) {
+        if (u * PAIR + 1 >= n_pages) {  // uniform: the last step has one page
 #pragma unroll
-        for (int i = 0; i < W::NK; ++i) r.k[i] = col >= 8 ? u32x4{0u, 0u, 0u, 0u} : r.k[i];
+          for (int i = 0; i < W::NK; ++i) r.k[i] = col >= 8 ? u32x4{0u, 0u, 0u, 0u} : r.k[i];
 #pragma unroll
-        for (int i = 0; i < DBLK; ++i) r.v[i] = grp >= 2 ? u32x4{0u, 0u, 0u, 0u} : r.v[i];
-        bias = grp >= 2 ? -__builtin_inff() : 0.f;
+          for (int i = 0; i < DBLK; ++i) r.v[i] = grp >= 2 ? u32x4{0u, 0u, 0u, 0u} : r.v[i];
+          bias = grp >= 2 ? -__builtin_inff() : 0.f;
+        }
       }
+      if constexpr (FP8) {
+        int t = u * PAIR + (PAIR == 2 && grp >= 2 ? 1 : 0);
+        t = t < n_pages ? t : n_pages - 1;
+        ksc = s_ksc[t];
+        vsc = s_vsc[t];
+      }
+      apply_step<D, NC>(r, ksc, vsc, bias, q, acc, m_run, l_run);
+    };
+#pragma unroll
+    for (int h = 0; h < NC; ++h) {
+#pragma unroll
+      for (int i = 0; i < DBLK; ++i) acc[h][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m_run[h] = kNoMax;
+      l_run[h] = 0.f;
     }
-    if constexpr (FP8) {
-      int t = u * PAIR + (PAIR == 2 && grp >= 2 ? 1 : 0);
-      t = t < n_pages ? t : n_pages - 1;
-      ksc = s_ksc[t];
-      vsc = s_vsc[t];
-    }
-    apply_step<D, 2>(r, ksc, vsc, bias, q, acc, m_run, l_run);
-  };
-  if (phase < n_steps) {
+    if (first >= n_steps) return;
     R ra, rb;
-    int u = phase;
+    int u = first;
     fetch(ra, u);
     while (true) {
-      fetch(rb, u + SP);
+      fetch(rb, u + by);
       apply(widen<D, FP8>(ra), u);
-      if ((u += SP) >= n_steps) break;
-      fetch(ra, u + SP);
+      if ((u += by) >= n_steps) break;
+      fetch(ra, u + by);
       apply(widen<D, FP8>(rb), u);
-      if ((u += SP) >= n_steps) break;
+      if ((u += by) >= n_steps) break;
     }
+  };
+  const int64_t slot0 = ((int64_t)kg * p.cmax + c) * MG;
+  // The partial of NC tiles from column c0, straight from the registers.
+  auto store = [&](int c0, const auto& acc, const auto& m_run, const auto& l_run) {
+    constexpr int NC = sizeof(m_run) / sizeof(float);
+#pragma unroll
+    for (int h = 0; h < NC; ++h) {
+      const float l = sum_xor32(sum_xor16(l_run[h]));
+      const int cg = c0 + h * 16 + col;
+      if (cg >= MG) continue;
+#pragma unroll
+      for (int i = 0; i < DBLK; ++i)
+        *(f32x4*)(p.part_o + (slot0 + cg) * D + 16 * i + 4 * grp) = acc[h][i];
+      if (grp == 0) p.part_ml[slot0 + cg] = make_float2(m_run[h], l);
+    }
+  };
+  const bool alone = n_steps <= kAloneSteps;  // uniform
+  if (alone && CP <= 2) {                     // SP >= 2: a wave for each tile
+    if (phase >= 2) return;
+    bf16x8 q1[1][KSTEPS];
+#pragma unroll
+    for (int s = 0; s < KSTEPS; ++s) q1[0][s] = phase ? q[1][s] : q[0][s];
+    f32x4 acc[1][DBLK];
+    float m_run[1], l_run[1];
+    stream(0, 1, q1, acc, m_run, l_run);
+    store(pr * 32 + phase * 16, acc, m_run, l_run);
+    return;
+  }
+  f32x4 acc[2][DBLK];
+  float m_run[2], l_run[2];
+  stream(phase < (alone ? 1 : SP) ? phase : n_steps, alone ? 1 : SP, q, acc, m_run, l_run);
+  if (alone) {
+    if (phase == 0) store(pr * 32, acc, m_run, l_run);
+    return;
   }
 
   // Merge of a pair's SP waves: each scales its accumulators to the columns'
@@ -319,7 +364,6 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
     }
   }
   __syncthreads();
-  const int64_t slot0 = ((int64_t)kg * p.cmax + c) * MG;
   if ((int)threadIdx.x < MG) {
     const int pc = threadIdx.x >> 5, cc = threadIdx.x & 31;
     float M = s_m[pc][cc], L = 0.f;
@@ -339,7 +383,7 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
     for (int i = 0; i < DBLK; ++i)
       *(f32x4*)&s_o[wave][col][16 * i + 4 * grp] = acc[h][i] * f;
     __syncthreads();
-    for (int e = threadIdx.x; e < CP * 16 * (D / 4); e += kPrefixThreads) {
+    for (int e = threadIdx.x; e < CP * 16 * (D / 4); e += 64 * WAVES) {
       const int cc = e / (D / 4), d4 = e - cc * (D / 4);  // column cc & 15 of pair cc >> 4
       const int pc = cc >> 4, cg = pc * 32 + h * 16 + (cc & 15);
       f32x4 o = *(const f32x4*)&s_o[pc][cc & 15][4 * d4];
@@ -351,22 +395,24 @@ __global__ __launch_bounds__(kPrefixThreads, 2) void prefix_kernel(GroupedParams
 }
 
 template <int D, int P, bool FP8>
-static const void* prefix_fn() {
-  return (const void*)&prefix_kernel<D, P, FP8>;
+static const void* prefix_fn(int waves) {
+  return waves == 8 ? (const void*)&prefix_kernel<D, P, FP8, 8>
+                    : (const void*)&prefix_kernel<D, P, FP8, 4>;
 }
 
 hipError_t launch_grouped_prefix(const GroupedParams& p, int grid, bool fp8, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
+  const int w = prefix_waves((int64_t)(p.num_seqs / p.group_size) * p.num_kv_heads);
   const void* fn;
   if (p.head_dim == 128)
-    fn = p.page_size == 16 ? (fp8 ? prefix_fn<128, 16, true>() : prefix_fn<128, 16, false>())
-                           : (fp8 ? prefix_fn<128, 32, true>() : prefix_fn<128, 32, false>());
+    fn = p.page_size == 16 ? (fp8 ? prefix_fn<128, 16, true>(w) : prefix_fn<128, 16, false>(w))
+                           : (fp8 ? prefix_fn<128, 32, true>(w) : prefix_fn<128, 32, false>(w));
   else
-    fn = p.page_size == 16 ? (fp8 ? prefix_fn<64, 16, true>() : prefix_fn<64, 16, false>())
-                           : (fp8 ? prefix_fn<64, 32, true>() : prefix_fn<64, 32, false>());
+    fn = p.page_size == 16 ? (fp8 ? prefix_fn<64, 16, true>(w) : prefix_fn<64, 16, false>(w))
+                           : (fp8 ? prefix_fn<64, 32, true>(w) : prefix_fn<64, 32, false>(w));
   GroupedParams arg = p;
   void* args[] = {(void*)&arg};
-  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kPrefixThreads), args, 0, s);
+  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(64 * w), args, 0, s);
 }
 
 }  // namespace dora

@@ -304,3 +304,34 @@ def test_grouped_combine_of_many_segments(dt, P, d, G, Hkv):
     seqs = [0, 1, 2, 3, 6, 7, 86, 87, 88, 90, 91, 120, 172, 173]
     assert max_abs_err(out, oracle_for(b, seqs), seqs) <= TOL[dt]
     assert (out.float() - run_decode(b).float()).abs().max().item() <= TOL[dt]
+
+
+@pytest.mark.parametrize("dt,P,d,G,M,Hkv,groups", [
+    (0, 16, 128, 7, 4, 4, 12),       # 28 columns: a wave for each tile
+    (1, 16, 64, 8, 8, 2, 12),        # 64 columns, fp8
+    (0, 32, 64, 9, 8, 2, 12),        # 72 columns: a wave for each pair of tiles
+    (1, 32, 128, 16, 8, 1, 12),      # 128 columns, fp8
+    (0, 16, 128, 16, 1, 8, 12),      # groups of one
+    (0, 16, 64, 2, 2, 8, 17),        # 136 (group, KV head) pairs: 4 waves
+    (1, 16, 128, 7, 10, 8, 17),      # ... 70 columns, fp8
+    (1, 32, 64, 16, 8, 11, 12),      # ... 128 columns
+])
+def test_grouped_short_prompts(dt, P, d, G, M, Hkv, groups):
+    """Prompts of 0 to 6 steps of 32 tokens, a last step of one 16-token page
+    among them: up to four steps the prefix kernel's waves write their partials
+    themselves, beyond they are merged.  With 8 and with 4 waves a workgroup."""
+    print(f"[case] short prompts dt={dt} P={P} d={d} G={G} M={M} Hkv={Hkv}", flush=True)
+    rng = np.random.default_rng(7 + G)
+    prompt = np.array([0, 1, 2, 3, 4, 5, 7, 8, 9, 10, 11, 12] + [2] * (groups - 12)) * 16 + 5
+    lens = (np.repeat(prompt, M) + rng.integers(P, 70, groups * M)).astype(np.int32)
+    pages = int(wl.pages_needed(lens, P).sum()) + 8
+    w = wl.Workload("sh", len(lens), G * Hkv, Hkv, d, P, dt, pages, "uniform", lo=1, hi=1)
+    b = wl.make_batch(w, device="cuda", seed_index=97 + dt, lengths=lens)
+    bt, shared = b.block_table_h.copy(), prompt // P
+    for m in range(len(lens)):
+        bt[m, :shared[m // M]] = bt[m - m % M, :shared[m // M]]
+    _set_tables(b, bt)
+    out, det = _grouped(b, M)
+    assert det.tolist() == (shared.tolist() if M > 1 else [0] * groups)
+    assert max_abs_err(out, oracle_for(b)) <= TOL[dt]
+    assert (out.float() - run_decode(b).float()).abs().max().item() <= TOL[dt]
