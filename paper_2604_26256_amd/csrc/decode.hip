@@ -448,7 +448,8 @@ __global__ __launch_bounds__(THREADS) void combine_kernel(CombineParams p) {
     b = (int)blockIdx.x / Hkv;
     g = (int)blockIdx.x - b * Hkv;
   }
-  merge_segment<THREADS>(p.part_o, p.part_ml, p.out, p.num_q_heads, p.group, p.head_dim, b, g, np,
+  merge_segment<THREADS>(p.part_o, p.part_ml, p.out, p.num_q_heads, p.group, p.head_dim, b, g, 0,
+                         p.group * (p.head_dim / 4), np,
                          [=](int k) { return 2 * (wa + k) + (k == 0 ? first_off : 0); });
 }
 

@@ -27,22 +27,24 @@ __device__ __forceinline__ void merge_piece(float2 ml, f32x4 o, float& M, float&
 }
 
 // Merge of np pieces of segment (b, g), piece k in slot slot_of(k), into its
-// output rows.  Threads are (head, 4 head-dim values) tasks x piece groups; each
-// folds its pieces into a running (max, normaliser, weighted sum) with one pass
-// of loads, and the groups are merged in LDS.
+// output rows: tasks task0 .. task0 + per - 1 of them, a task being a head and 4
+// head-dim values.  Threads are tasks x piece groups; each folds its pieces into a
+// running (max, normaliser, weighted sum) with one pass of loads, and the groups
+// are merged in LDS.
 template <int THREADS, typename SlotOf>
 __device__ __forceinline__ void merge_segment(const float* part_o, const float2* part_ml,
                                               uint16_t* out, int num_q_heads, int G, int D, int b,
-                                              int g, int np, SlotOf slot_of) {
+                                              int g, int task0, int per, int np, SlotOf slot_of) {
   __shared__ float sM[THREADS], sS[THREADS];
   __shared__ f32x4 sAcc[THREADS];
   const int t = threadIdx.x;
-  const int tasks = G * (D / 4);
-  const int tasks_r = (tasks + 63) & ~63;
-  const int groups = THREADS / tasks_r;  // >= 1 since tasks <= 512
+  const int tasks = G * (D / 4) - task0 < per ? G * (D / 4) - task0 : per;  // <= 0: none
+  const int tasks_r = (per + 63) & ~63;
+  const int groups = THREADS / tasks_r;  // >= 1 since per <= 512
   const int task = t % tasks_r, sg = t / tasks_r;
   const bool active = task < tasks && sg < groups;
-  const int n = active ? task / (D / 4) : 0, d4 = active ? task - n * (D / 4) : 0;
+  const int n = active ? (task0 + task) / (D / 4) : 0;
+  const int d4 = active ? task0 + task - n * (D / 4) : 0;
   float M = -__builtin_inff(), S = 0.f;
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
   if (active) {
@@ -61,18 +63,7 @@ __device__ __forceinline__ void merge_segment(const float* part_o, const float2*
         }
       }
 #pragma unroll
-      for (int i = 0; i < kCombineBatch; ++i) {
-        if (ml[i].x > M) {
-          const float sc = __builtin_amdgcn_exp2f(M - ml[i].x);
-          acc = acc * sc + o[i];
-          S = S * sc + ml[i].y;
-          M = ml[i].x;
-        } else if (ml[i].x > -__builtin_inff()) {
-          const float wgt = __builtin_amdgcn_exp2f(ml[i].x - M);
-          acc += wgt * o[i];
-          S += wgt * ml[i].y;
-        }
-      }
+      for (int i = 0; i < kCombineBatch; ++i) merge_piece(ml[i], o[i], M, S, acc);
     }
   }
   sM[t] = M;

@@ -39,10 +39,11 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void segment_kernel(SegmentParam
   const int lane = threadIdx.x & 63, wave = uni((int)threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
   const int Hkv = p.num_kv_heads, G = p.group;
-  // chunk-major: the workgroups that have work come first
-  const int segs = p.num_seqs * Hkv;
-  const int c = (int)blockIdx.x / segs, seg = (int)blockIdx.x - c * segs;
-  const int b = seg / Hkv, g = seg - b * Hkv;
+  // Chunk-major: the workgroups that have work come first.
+  const int c = (int)blockIdx.y;
+  const int b = (int)blockIdx.x / Hkv;
+  const int g = (int)blockIdx.x - b * Hkv;
+  const int seg = b * Hkv + g;
   const int64_t row0 = (int64_t)b * p.num_q_heads + (int64_t)g * G;
   const int L = min(p.seq_lens[b], p.stride * P);  // a contract violation stays in bounds
   const int j0 = c * p.seg_pages;  // < stride
@@ -141,17 +142,19 @@ done:
   }
 }
 
-// The combine of the segment kernel: one workgroup per segment, which merges
-// the segment's chunks where it has more than one.
+// The combine of the segment kernel: workgroup (seg, part) merges the chunks of a
+// segment that has more than one, for the tasks part * per .. of it (all, or an
+// equal share).
 template <int THREADS>
-__global__ __launch_bounds__(THREADS) void combine_chunks_kernel(SegmentParams p) {
+__global__ __launch_bounds__(THREADS) void combine_chunks_kernel(SegmentParams p, int per) {
   const int seg = (int)blockIdx.x;
   const int b = seg / p.num_kv_heads, g = seg - b * p.num_kv_heads;
   const int n = pages_of(p.seq_lens[b], p.page_size, p.stride);
   if (n <= p.seg_pages) return;
   const int64_t slot0 = (int64_t)seg * p.seg_chunks;
   merge_segment<THREADS>(p.part_o, p.part_ml, p.out, p.num_q_heads, p.group, p.head_dim, b, g,
-                         (n + p.seg_pages - 1) / p.seg_pages, [=](int k) { return slot0 + k; });
+                         (int)blockIdx.y * per, per, (n + p.seg_pages - 1) / p.seg_pages,
+                         [=](int k) { return slot0 + k; });
 }
 
 // Tokens per step: 16-token pages go in pairs while the workgroups are at most
@@ -181,12 +184,22 @@ hipError_t launch_segments(const SegmentParams& p, bool fp8, hipStream_t s) {
                          : (fp8 ? segment_fn<64, 32, true>(grid) : segment_fn<64, 32, false>(grid));
   SegmentParams arg = p;
   void* args[] = {(void*)&arg};
-  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(64 * kSegWaves), args, 0, s);
+  return hipLaunchKernel(fn,
+                         dim3((unsigned)(p.num_seqs * p.num_kv_heads), (unsigned)p.seg_chunks),
+                         dim3(64 * kSegWaves), args, 0, s);
 }
 
+// Few segments of many chunks: one workgroup of 512 threads would walk a segment's
+// chunks in rounds of 4 x (512 / tasks), about 0.7 us each, so its tasks are shared
+// out until two rounds do (or 64 tasks are left, the unit of a thread group).
 hipError_t launch_combine_chunks(const SegmentParams& p, hipStream_t s) {
   const int segs = p.num_seqs * p.num_kv_heads;
-  hipLaunchKernelGGL(combine_chunks_kernel<512>, dim3((unsigned)segs), dim3(512), 0, s, p);
+  const int tasks = p.group * (p.head_dim / 4);
+  int parts = 1;
+  while (tasks > 64 * parts && p.seg_chunks * (tasks / parts) > 8 * 512 && 2 * parts * segs <= 1024)
+    parts *= 2;
+  hipLaunchKernelGGL(combine_chunks_kernel<512>, dim3((unsigned)segs, (unsigned)parts), dim3(512), 0,
+                     s, p, (tasks + parts - 1) / parts);
   return hipGetLastError();
 }
 
