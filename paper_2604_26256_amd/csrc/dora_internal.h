@@ -84,6 +84,7 @@ struct SegmentParams {
   int32_t num_seqs, num_q_heads, num_kv_heads, group, stride, head_dim, page_size;
   int32_t seg_pages;   // pages per workgroup
   int32_t seg_chunks;  // workgroups (chunks) per segment
+  int32_t rotate;      // set by launch_segments
   float scale_log2;
 };
 

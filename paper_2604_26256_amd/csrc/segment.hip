@@ -41,8 +41,9 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void segment_kernel(SegmentParam
   const int Hkv = p.num_kv_heads, G = p.group;
   // Chunk-major: the workgroups that have work come first.
   const int c = (int)blockIdx.y;
-  const int b = (int)blockIdx.x / Hkv;
+  int b = (int)blockIdx.x / Hkv;
   const int g = (int)blockIdx.x - b * Hkv;
+  if (p.rotate) b = (b + c + (c >> 2)) % p.num_seqs;
   const int seg = b * Hkv + g;
   const int64_t row0 = (int64_t)b * p.num_q_heads + (int64_t)g * G;
   const int L = min(p.seq_lens[b], p.stride * P);  // a contract violation stays in bounds
@@ -183,6 +184,16 @@ hipError_t launch_segments(const SegmentParams& p, bool fp8, hipStream_t s) {
     fn = p.page_size == 16 ? (fp8 ? segment_fn<64, 16, true>(grid) : segment_fn<64, 16, false>(grid))
                          : (fp8 ? segment_fn<64, 32, true>(grid) : segment_fn<64, 32, false>(grid));
   SegmentParams arg = p;
+  // Workgroups go to the 8 XCDs in turn, and there to the 4 shader engines.  With an
+  // even number of sequences all chunks of a long row would be on some of these
+  // only, so the sequences are rotated from chunk to chunk: by one, for the XCDs or
+  // engines, and by one more every four chunks, for their combinations (4 fp8 rows of
+  // 8 KV heads, one of 16,900 tokens: 28.0 -> 21.5 us; 8 bf16 rows of one KV head, one
+  // of 40,500 tokens among rows of 48: 25.3 -> 19.0).  An odd number spreads by itself
+  // and is only slower for it (3 fp8 rows of 8 KV heads: 17.7 -> 22.1); rows of few
+  // chunks gain nothing (8 of them: 8.3 -> 8.8).  A grid padded by one sequence spreads
+  // as well, but leaves CUs idle where all rows are full (13.8 -> 16.9).
+  arg.rotate = p.seg_chunks > 16 && p.num_seqs % 2 == 0;
   void* args[] = {(void*)&arg};
   return hipLaunchKernel(fn,
                          dim3((unsigned)(p.num_seqs * p.num_kv_heads), (unsigned)p.seg_chunks),

@@ -314,7 +314,7 @@ def test_segment_kernel_edges(dt, d, P, Hkv, G, stride):
 
 @pytest.mark.parametrize("dt,d,P,Hkv,G,lens", [
     (0, 128, 16, 1, 16, [20000, 48, 9000, 0, 300, 16]),      # 512 tasks, 79 chunks of 256
-    (1, 128, 32, 8, 4, [14000, 700, 3000, 1]),               # four rows of 8 heads
+    (1, 128, 32, 8, 4, [14000, 700, 3000, 1]),               # four rows of 8 heads: rotated
     (1, 64, 16, 2, 1, [17000, 40]),                          # 16 tasks
     (0, 128, 32, 1, 6, [40000]),                             # one row, chunks of 512
     (0, 64, 32, 1, 8, [36000, 36000]),
@@ -322,8 +322,9 @@ def test_segment_kernel_edges(dt, d, P, Hkv, G, stride):
     (1, 128, 16, 4, 7, [9000, 100, 5000]),                   # an odd number of rows
 ])
 def test_segment_kernel_many_chunks(dt, d, P, Hkv, G, lens):
-    """Rows of many chunks: the combine shares a segment's tasks out.  Against the
-    oracle and against stream-K; bitwise the same when repeated."""
+    """Rows of many chunks: the combine shares a segment's tasks out, and an even
+    number of rows is rotated from chunk to chunk.  Against the oracle and against
+    stream-K; bitwise the same when repeated."""
     print(f"[case] chunks dt={dt} d={d} P={P} Hkv={Hkv} G={G} rows={lens}", flush=True)
     lens = np.array(lens, np.int32)
     w = _w(B=len(lens), Hq=G * Hkv, Hkv=Hkv, d=d, P=P, dt=dt, lens=lens)
