@@ -2,7 +2,8 @@
  * dora_measure.h — measurement entry points of libdora.
  *
  * They are not part of the method.  They let a benchmark time the kernels of
- * one decode call separately, and compare the decode kernel with a plain
+ * one decode call separately, tell which ones they are, and compare the decode
+ * kernel with a plain
  * streaming read that has the decode kernel's access pattern (random 4 KiB
  * tiles, 16-byte non-temporal loads): the achievable-bandwidth reference next
  * to the HBM peak in the decode kernel's roofline.  The conventions of dora.h
@@ -20,16 +21,24 @@ extern "C" {
 
 /* dora_decode_attn with per-kernel timing.  Same arguments, results and
  * errors as dora_decode_attn, plus `events`: three caller-created hipEvent_t
- * (non-NULL) recorded on `stream` before the first decode kernel (events[0]),
- * between it and its combine kernel (events[1]) and after the last combine
- * kernel (events[2]).  DORA_ERR_INVALID_ARG if events or one of its entries is
- * NULL.  No event is recorded when an error is returned before any launch. */
+ * (non-NULL) recorded on `stream` before the first decode (or segment) kernel
+ * (events[0]), between it and its combine kernel (events[1]) and after the last
+ * combine kernel (events[2]).  A batch whose segments run whole has no combine:
+ * nothing lies between events[1] and events[2] then.  DORA_ERR_INVALID_ARG if
+ * events or one of its entries is NULL.  No event is recorded when an error is
+ * returned before any launch. */
 dora_status dora_decode_attn_timed(const dora_decode_desc* desc,
                                    const void* q, const void* k_pages, const void* v_pages,
                                    const int32_t* block_table, const int32_t* seq_lens,
                                    const int32_t* version_ids, void* out,
                                    void* workspace, size_t workspace_bytes,
                                    dora_stream_t stream, void* const* events);
+
+/* Pages per workgroup of the segment kernel where dora_decode_attn cuts the (first
+ * launch of the) batch per segment on the current device: block_table_stride for
+ * whole segments, less for chunks.  0 where it takes the stream-K decode kernel,
+ * and for an invalid or unsupported descriptor or an empty batch. */
+int32_t dora_decode_segment_pages(const dora_decode_desc* desc);
 
 /* Streaming-read reference kernel.  Reads n_tiles tiles of tile_bytes bytes,
  * tile i starting at base + tiles[i] * tile_bytes, with 16-byte non-temporal

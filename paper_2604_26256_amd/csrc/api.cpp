@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include "dora_internal.h"
+#include "dora_measure.h"
 
 using namespace dora;
 
@@ -41,6 +42,30 @@ dora_status check_desc(const dora_decode_desc* d) {
   return DORA_OK;
 }
 
+// Longest row, in tokens, that the segment kernel takes whole.
+constexpr int kWholeMost = 2048;
+static_assert(kWholeMost / 16 <= 64 * kSegWaves, "a lane holds each page of its wave");
+
+// Whether the segment kernel takes segments of `tokens` whole.  Past a length the
+// longest sequence of a skewed batch ends alone; past a number, workgroups of 256
+// threads that have a page or two each start no faster than the stream-K decode
+// streams, whose own start grows with the sequences: their difference follows
+// segs - 0.55 seqs (7,880 bf16 segments of 16 tokens, 985 sequences, 21.3 us by
+// stream-K and 39.0 whole; 6,546 of 32 tokens and as many sequences 29.8 and 14.9).
+bool whole_segments(const dora_decode_desc& d, int64_t segs, int64_t tokens) {
+  const bool fp8 = d.kv_dtype == DORA_KV_FP8_E4M3;
+  int64_t most;
+  if (d.head_dim == 64)
+    most = fp8 ? (tokens <= kWholeMost ? 8000 : -1) : tokens <= 1536 ? 6000 : -1;
+  else if (fp8)
+    most = tokens <= 1024 ? 5000 : tokens <= 1536 ? 3500 : -1;
+  else if (d.page_size == 32)
+    most = tokens <= 512 ? 1500 : tokens <= 1024 ? 500 : -1;
+  else
+    most = tokens <= 768 ? 2000 : tokens <= 1280 ? 1000 : -1;
+  return segs - segs / d.num_kv_heads * 11 / 20 <= most;
+}
+
 // The split of the segment kernel for a launch over `segs` (sequence, KV head)
 // segments: pages per workgroup, or 0 where the stream-K decode runs instead.  A
 // caller that sets how the work is cut gets that cut.
@@ -50,51 +75,41 @@ dora_status check_desc(const dora_decode_desc* d) {
 // 4.5 us; the stream-K call takes 12-20 us however little there is to do.  So
 // few segments are cut into chunks of 256 or 512 tokens as long as all of them
 // fit the chip about once (two workgroups per CU, and some that are empty), and
-// any number of segments goes whole up to a length past which the longest
-// sequence of a skewed batch would end alone: 1,280 tokens for bf16 (1,024 in
-// 32-token pages, which the stream-K decode streams faster; no 512-token chunks
-// either), 1,536 for fp8, 2,048 for head dim 64.  Past that length chunks, in
+// more go whole up to a length and a number.  Past that length chunks, in
 // several rounds of workgroups, compete with a stream-K call whose own costs
 // (every wave's page prefix, its search, the cuts) weigh up to about 50 us: the
 // chunks go on to 1,024 workgroups of 256 tokens and, for fp8, to 1,280 of 512
 // tokens, 2,048 for head dim 64 (2-4 KiB a page and head, for which stream-K
-// pays as much per page as for four times the bytes).
-//   Over 700 random batches of up to 8,192 tokens (page sizes, head dims,
-// dtypes, 1-8 KV heads, four length mixes) the first lines are 1.75x as fast by
-// geometric mean, 3 of them 4-7% slower.  The lines past the whole length: over
-// 737 more batches that they take (up to 9,000 tokens, six mixes) 1.25x (fp8
-// 1.26x, bf16 1.11x); 7 are more than 3% slower, most of them a long sequence among
-// very short ones.  512-token chunks for bf16 too would gain 5-8% up to 896
-// workgroups where the rows are full and lose where they are not (64 sequences
-// of 28 / 4 heads, 320 tokens at the median, 1,500 at most: 17.4 -> 18.2 us).
-//   Either side of the lines, segment / stream-K: 8 segments of 4,096 fp8 tokens
-// 9.7 / 18.2 us; 128 of 2,496 bf16 19.3 / 22.3; 176 of 1,264 15.5 / 17.9.  Times
-// as fast as stream-K, 512-token chunks, by the number of workgroups (the worst
-// of a bin): fp8, head dim 128, 16-token pages, up to 768 1.20 (1.05), 1,280 1.17
-// (0.96), 1,536 1.12 (0.89), 2,048 1.08 (0.88); fp8, head dim 64, 768 1.44
-// (1.31), 2,048 1.31 (0.83); bf16 in 32-token pages 0.95 and less.  1,024-token
-// chunks gain less than these in every bin.
+// pays as much per page as for four times the bytes).  32-token bf16 pages of head
+// dim 128, which stream-K streams faster and whose workgroups are two per CU, stop at
+// 256 of either, 640 of 256 tokens below 2,048 tokens.  Rows past 32,768 tokens go in
+// 512s: the combine of more than 128 chunks costs more than the shorter ones gain
+// (one row of 120,000 bf16 tokens, 16 heads: 28 us in 256s, 21 in 512s).
+//   The lines lie where nearly no batch loses: of 15,563 random ones that a rule on
+// shorter rows and fewer segments had given the segment kernel (1 to 9,000 segments,
+// up to 200,000 tokens, all geometries, seven length mixes, one long row among short
+// ones among them), 11 take more than 3% longer than by stream-K, the worst 10%.
+// Times the stream-K call, by geometric mean (the worst of a bin): chunks of 256 up to
+// 768 workgroups 0.51-0.80 (1.03), of 32-token bf16 pages up to 256 0.76 (0.97) and
+// beyond, past 2,048 tokens, 0.93 (1.23, not taken); chunks of 512, fp8 up to 1,280
+// 0.57-0.83 (1.02), 2,048 for head dim 64 0.70 (0.99), bf16 up to 640 0.77 (1.10).
 int segment_split(const dora_decode_desc& d, int64_t segs, int64_t waves) {
   if (d.num_waves > 0 || d.min_range_pages > 0) return 0;
   const int64_t tokens = (int64_t)d.block_table_stride * d.page_size;
-  const bool wide_pages = d.kv_dtype == DORA_KV_BF16 && d.page_size == 32;
-  auto workgroups = [&](int chunk) { return segs * ((tokens + chunk - 1) / chunk); };
+  const bool fp8 = d.kv_dtype == DORA_KV_FP8_E4M3;
+  const bool wide_pages = !fp8 && d.page_size == 32, d128 = d.head_dim == 128;
   auto fits = [&](int chunk, int64_t most) {  // each workgroup of a split has a partial slot
-    return tokens >= 4 * chunk && workgroups(chunk) <= most && workgroups(chunk) <= 2 * waves;
+    const int64_t workgroups = segs * ((tokens + chunk - 1) / chunk);
+    return workgroups <= most && workgroups <= 2 * waves;
   };
-  if (fits(256, 768)) return 256 / d.page_size;
-  if (!wide_pages && fits(512, 640)) return 512 / d.page_size;
-  const int64_t whole = wide_pages                        ? 1024
-                        : d.head_dim == 64                ? 2048
-                        : d.kv_dtype == DORA_KV_FP8_E4M3  ? 1536
-                                                          : 1280;
-  static_assert(2048 / 16 <= 64 * kSegWaves, "a lane holds each page of its wave");
-  if (tokens <= whole) return d.block_table_stride;
+  const bool in_256 = tokens >= (wide_pages && d128 ? 768 : 1024) && tokens <= 32768;
+  const int64_t most_256 = !d128 || fp8 ? 768 : !wide_pages ? 1024 : tokens < 2048 ? 640 : 256;
+  if (in_256 && fits(256, most_256)) return 256 / d.page_size;
+  if (tokens >= 2048 && fits(512, !wide_pages ? 640 : d128 ? 256 : 384)) return 512 / d.page_size;
+  if (whole_segments(d, segs, tokens)) return d.block_table_stride;
   if (wide_pages) return 0;
-  if (workgroups(256) <= 1024 && workgroups(256) <= 2 * waves) return 256 / d.page_size;
-  if (d.kv_dtype == DORA_KV_BF16) return 0;
-  const int64_t most = d.head_dim == 64 ? 2048 : 1280;
-  return workgroups(512) <= most && workgroups(512) <= 2 * waves ? 512 / d.page_size : 0;
+  if (in_256 && fits(256, 1024)) return 256 / d.page_size;
+  return fp8 && fits(512, d128 ? 1280 : 2048) ? 512 / d.page_size : 0;
 }
 
 // Whether a grouped call whose caller does not ask for the shared page counts
@@ -196,6 +211,12 @@ size_t dora_decode_workspace_bytes(const dora_decode_desc* desc) {
 int64_t dora_decode_num_waves(const dora_decode_desc* desc) {
   if (check_desc(desc) != DORA_OK) return 0;
   return decode_waves(*desc);
+}
+
+int32_t dora_decode_segment_pages(const dora_decode_desc* desc) {
+  if (check_desc(desc) != DORA_OK || desc->num_seqs == 0) return 0;
+  const int64_t seqs = desc->num_seqs < kMaxSeqsPerLaunch ? desc->num_seqs : kMaxSeqsPerLaunch;
+  return segment_split(*desc, seqs * desc->num_kv_heads, decode_waves(*desc));
 }
 
 }  // extern "C"

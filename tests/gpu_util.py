@@ -74,6 +74,15 @@ def decode_waves(b: wl.Batch, **kw) -> int:
     return d.dora_decode_num_waves(desc)
 
 
+def segment_pages(b: wl.Batch, **kw) -> int:
+    """Pages per workgroup of b's decode where it runs per segment, 0 where stream-K."""
+    d = lib()
+    return d.dora_decode_segment_pages(d.make_decode_desc(
+        num_seqs=b.w.num_seqs, num_q_heads=b.w.num_q_heads, num_kv_heads=b.w.num_kv_heads,
+        head_dim=b.w.head_dim, page_size=b.w.page_size, block_table_stride=b.stride,
+        num_pages=b.w.num_pages, kv_dtype=b.w.kv_dtype, **kw))
+
+
 def cut_segments(lengths, page_size, stride, num_kv_heads, waves, min_range=8):
     """The (sequence, KV head) segments a launch cuts across wavefronts, from
     the work split the header documents: T = Hkv x (pages of the batch)

@@ -336,3 +336,48 @@ def test_prepared_decode_checks_arguments_like_the_plain_call(d):
             fn(q, k, v, bt, lens, None, out, num_kv_heads=Hkv, page_size=32)
     empty = d.PreparedDecode(q[:0], k, v, bt[:0], lens[:0], None, out[:0], **kw)
     assert empty() is not None and empty().numel() == 0
+
+
+@pytest.mark.parametrize("dt,d_,P,B,Hkv,stride,tokens", [
+    # (bf16, 128, 16): chunks of 256 up to 1,024 workgroups, of 512 up to 640, whole
+    (0, 128, 16, 11, 2, 64, 256),        # 1,024 tokens
+    (0, 128, 16, 11, 2, 63, 63 * 16),    # shorter rows whole
+    (0, 128, 16, 128, 2, 64, 256),       # 1,024 workgroups ...
+    (0, 128, 16, 257, 1, 64, 64 * 16),   # ... and past them: whole up to 1,280 tokens ...
+    (0, 128, 16, 257, 1, 81, 0),         # ... and stream-K past those
+    (0, 128, 16, 11, 9, 189, 512),       # 594 of 512 tokens
+    (0, 128, 16, 12, 9, 189, 0),         # 648
+    (0, 128, 16, 1, 1, 2048, 256),       # rows of 32,768 tokens
+    (0, 128, 16, 1, 1, 2049, 512),       # longer ones in 512s
+    (0, 128, 16, 2000, 1, 2, 32),        # many short segments: segments - 0.55 sequences
+    (0, 128, 16, 267, 8, 2, 32),         # 2,136 - 146 ...
+    (0, 128, 16, 269, 8, 2, 0),          # 2,152 - 147: past 2,000
+    (0, 128, 16, 4400, 1, 2, 32),
+    # 32-token bf16 pages of head dim 128
+    (0, 128, 32, 16, 1, 24, 256),        # from 768 tokens
+    (0, 128, 32, 16, 1, 23, 23 * 32),
+    (0, 128, 32, 40, 4, 32, 256),        # 640 workgroups below 2,048 tokens ...
+    (0, 128, 32, 41, 4, 32, 32 * 32),    # ... whole past them
+    (0, 128, 32, 32, 1, 64, 256),        # 256 from 2,048 tokens on
+    (0, 128, 32, 33, 1, 64, 512),        # 132 of 512
+    (0, 128, 32, 65, 1, 64, 0),          # 260
+    (0, 128, 32, 1000, 1, 32, 32 * 32),  # 1,000 - 550 whole segments of 1,024 tokens
+    (0, 128, 32, 200, 4, 32, 0),         # 800 - 110
+    # fp8
+    (1, 128, 16, 96, 1, 128, 256),       # 768 workgroups
+    (1, 128, 16, 128, 2, 80, 80 * 16),
+    (1, 128, 16, 20, 16, 128, 512),      # 1,280 of 512 ...
+    (1, 128, 16, 21, 16, 128, 0),        # ... and past them
+    (1, 64, 16, 512, 1, 129, 0),         # head dim 64: 2,560 of 512
+    (1, 64, 16, 408, 1, 129, 512),       # 2,040
+    (1, 64, 16, 512, 1, 128, 128 * 16),  # whole up to 2,048 tokens
+])
+def test_segment_split_lines(d, dt, d_, P, B, Hkv, stride, tokens):
+    """Which cut a decode takes at the lines of the rule on sizes: tokens per
+    workgroup of the segment kernel, 0 for stream-K; always stream-K where the
+    caller sets the cut."""
+    kw = dict(num_seqs=B, num_q_heads=4 * Hkv, num_kv_heads=Hkv, head_dim=d_, page_size=P,
+              block_table_stride=stride, num_pages=1000, kv_dtype=dt)
+    assert d.dora_decode_segment_pages(d.make_decode_desc(**kw)) * P == tokens
+    for cut in ({"num_waves": 100}, {"min_range_pages": 8}):
+        assert d.dora_decode_segment_pages(d.make_decode_desc(**kw, **cut)) == 0

@@ -10,7 +10,7 @@ import torch
 
 import workloads as wl
 from gpu_util import (TOL, cut_segments, decode_waves, gpu_batch, lib, max_abs_err, oracle_for,
-                      page_chunks, run_decode)
+                      page_chunks, run_decode, segment_pages)
 
 pytestmark = pytest.mark.gpu
 
@@ -329,6 +329,7 @@ def test_segment_kernel_many_chunks(dt, d, P, Hkv, G, lens):
     lens = np.array(lens, np.int32)
     w = _w(B=len(lens), Hq=G * Hkv, Hkv=Hkv, d=d, P=P, dt=dt, lens=lens)
     b = gpu_batch(w, lengths=lens, seed_index=400 + G)
+    assert 0 < segment_pages(b) * 16 < b.stride
     out = run_decode(b, out=torch.full_like(b.q, float("nan")))
     assert max_abs_err(out, oracle_for(b)) <= TOL[dt]
     assert torch.equal(run_decode(b), out)
