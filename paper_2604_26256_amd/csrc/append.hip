@@ -2,9 +2,9 @@
 // current token (counted in seq_lens, the token the next decode step attends
 // with; the per-token step of Sec. 2.2) is stored into its page slot.
 //
-// One workgroup per sequence.  bf16 pages take a plain store.  fp8 pages keep
-// one fp32 scale per page for K and one for V; the paper leaves the policy
-// open, and the one taken is grow-only:
+// bf16 pages take a plain store, one workgroup per sequence.  fp8 pages keep one
+// fp32 scale per page for K and one for V (a workgroup each); the paper leaves the
+// policy open, and the one taken is grow-only:
 //   amax = max |x| over the token's Hkv x d values
 //   fresh = max(amax / 448, 2^-126)          (always a normal number)
 //   slot 0:                          s = fresh
@@ -26,10 +26,6 @@
 // no V store).  A page whose fp8 scale grows, about one append in ten, is
 // requantised by table: as byte-wise arithmetic, one workgroup for K and V,
 // that took 390 us for the same four calls.
-//   Cost of the two workgroups a sequence: small bf16 batches whose pools lie in
-// the caches take 0.2-0.4 us a call more than with one (four calls: 64 sequences
-// of 4 heads 10.4 -> 11.2 us, 128 of 8 heads 15.3 -> 16.8; 512 of 8 heads 33.4 ->
-// 32.0; fp8 at every size 3-4x faster, 64 of 4 heads 101 -> 24 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -77,17 +73,6 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float x) {
   return sign | code;
 }
 
-// Byte offset of element (head h, token slot t, dim i) inside a page.
-template <int E>
-__device__ __forceinline__ int64_t k_offset(int d, int P, int h, int t, int i) {
-  constexpr int X = 16 / E;
-  return ((((int64_t)h * (d / X) + i / X) * P + t) * X + i % X) * E;
-}
-template <int E>
-__device__ __forceinline__ int64_t v_offset(int d, int P, int h, int t, int i) {
-  return (((int64_t)h * d + i) * P + t) * E;
-}
-
 // The four bf16 values of one 8-byte load.
 struct Quad {
   u32x2 w;
@@ -96,37 +81,25 @@ struct Quad {
   }
 };
 
-// K: store values 4i .. 4i+3 of the token, a quarter (bf16: half) of a 16-byte
-// chunk, into slot `slot` of the page.  Each chunk is the only write to its
-// 128-byte line, so the stores are non-temporal: they then do not hold L2 lines
-// that the V stores of the same call need (four calls in a row, each
-// over another pool: 512 bf16 sequences 46.9 -> 38.8 us, 1,024 fp8 ones 107 ->
-// 94 us; after a 1 GiB read level; non-temporal V stores as well: 50 and 89 us).
-template <bool FP8>
+// fp8 K: store values 4i .. 4i+3 of the token, a quarter of a 16-byte chunk, into
+// slot `slot` of the page.  Each chunk is the only write to its 128-byte line, so
+// the stores are non-temporal: they then do not hold L2 lines that the V stores of
+// the same call need (four calls in a row over 1,024 sequences, each over another
+// pool: 107 -> 94 us; after a 1 GiB read level; non-temporal V stores as well: 89).
 __device__ __forceinline__ void store_k(uint8_t* __restrict__ page, int P, int slot, int i, Quad x,
                                         float s) {
-  if constexpr (!FP8) {
-    const int chunk = i >> 1;  // 8 values
-    __builtin_nontemporal_store(x.w, (u32x2*)(page + ((int64_t)chunk * P + slot) * 16 +
-                                              8 * (i & 1)));
-  } else {
-    uint32_t q = 0;
+  uint32_t q = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) q |= f32_to_e4m3(__fdiv_rn(x.value(k), s)) << (8 * k);
-    const int chunk = i >> 2;  // 16 values
-    __builtin_nontemporal_store(q, (uint32_t*)(page + ((int64_t)chunk * P + slot) * 16 +
-                                               4 * (i & 3)));
-  }
+  for (int k = 0; k < 4; ++k) q |= f32_to_e4m3(__fdiv_rn(x.value(k), s)) << (8 * k);
+  const int chunk = i >> 2;  // 16 values
+  __builtin_nontemporal_store(q, (uint32_t*)(page + ((int64_t)chunk * P + slot) * 16 +
+                                             4 * (i & 3)));
 }
 
-// V: store value `row` (head, dim) of the token into its row of the page.
-template <bool FP8>
+// fp8 V: store value `row` (head, dim) of the token into its row of the page.
 __device__ __forceinline__ void store_v(uint8_t* __restrict__ page, int P, int slot, int row,
                                         uint16_t x, float s) {
-  if constexpr (!FP8)
-    *(uint16_t*)(page + ((int64_t)row * P + slot) * 2) = x;
-  else
-    page[(int64_t)row * P + slot] = (uint8_t)f32_to_e4m3(__fdiv_rn(bf16_bits_to_f32(x), s));
+  page[(int64_t)row * P + slot] = (uint8_t)f32_to_e4m3(__fdiv_rn(bf16_bits_to_f32(x), s));
 }
 
 // The 16 codes of a piece through a page's code table; byte k stays as it is
@@ -177,7 +150,24 @@ __device__ void requantise(uint8_t* __restrict__ page, const uint8_t* lut, int n
   }
 }
 
-// One workgroup per (sequence, K or V), blockDim.x threads (a multiple of 64).
+// Page and slot (in the page) of sequence b's current token; the page is -1 where
+// there is nothing to append or the page may not be written (never outside the
+// pool or into another version's page: reported by the first thread).
+__device__ __forceinline__ int64_t locate(const AppendParams& p, int b, int& slot) {
+  const int P = p.page_size, L = p.seq_lens[b];
+  slot = 0;
+  if (L <= 0) return -1;
+  const int t = L - 1, j = t / P;
+  slot = t - j * P;
+  bool ok = L <= p.stride * P;
+  const int64_t page_id = ok ? (int64_t)p.block_table[(int64_t)b * p.stride + j] : -1;
+  ok = ok && page_id >= 0 && page_id < p.num_pages;
+  if (ok && p.page_owner && p.version_ids) ok = p.page_owner[page_id] == p.version_ids[b];
+  if (!ok && threadIdx.x == 0 && p.dev_status) *p.dev_status = (int32_t)DORA_ERR_DEVICE_CHECK;
+  return ok ? page_id : -1;
+}
+
+// fp8: one workgroup per (sequence, K or V), blockDim.x threads (a multiple of 64).
 // K and V have a scale each and share no byte, so nothing crosses the two.
 // Thread i holds values 4i .. 4i+3 of K; of V it holds values i, i + T, i +
 // 2T, i + 3T, so that neighbouring lanes store into neighbouring rows (a
@@ -185,7 +175,7 @@ __device__ void requantise(uint8_t* __restrict__ page, const uint8_t* lut, int n
 // wide tokens, are read again when stored.  The dependent memory rounds are:
 // length (and the token, which does not wait for it), block-table entry, page
 // scale.
-template <bool FP8, bool IS_K>
+template <bool IS_K>
 __device__ __forceinline__ void append_side(const AppendParams& p, uint8_t* pages, float* scales,
                                             const uint16_t* token) {
   __shared__ float sred[kAppendMaxThreads / 64];
@@ -203,80 +193,106 @@ __device__ __forceinline__ void append_side(const AppendParams& p, uint8_t* page
     for (int k = 0; k < 4; ++k)
       if (tid + k * T < n) vq[k] = x[tid + k * T];
   }
-  const int L = p.seq_lens[b];
-  if (L <= 0) return;  // nothing to append
-  const int t = L - 1, j = t / P, slot = t - j * P;
-  bool ok = L <= p.stride * P;
-  const int64_t page_id = ok ? (int64_t)p.block_table[(int64_t)b * p.stride + j] : -1;
-  ok = ok && page_id >= 0 && page_id < p.num_pages;
-  if (ok && p.page_owner && p.version_ids) ok = p.page_owner[page_id] == p.version_ids[b];
-  if (!ok) {  // never write outside the pool or into another version's page
-    if (tid == 0 && p.dev_status) *p.dev_status = (int32_t)DORA_ERR_DEVICE_CHECK;
-    return;
-  }
-  uint8_t* page = pages + page_id * ((int64_t)n * P * (FP8 ? 1 : 2));
-  float s = 0.f;
-  if constexpr (FP8) {
-    // Thread 0 reads the page's scale and publishes it in LDS before the
-    // reduction's barrier; it alone stores the new one, after it.
-    if (tid == 0) sold = slot > 0 ? scales[page_id] : 0.f;
-    float m = 0.f;
-    if constexpr (IS_K) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) m = fmaxf(m, fabsf(kq.value(k)));
-      for (int i = tid + T; 4 * i < n; i += T) {
-        const Quad y{*(const u32x2*)(x + 4 * i)};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) m = fmaxf(m, fabsf(y.value(k)));
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) m = fmaxf(m, fabsf(bf16_bits_to_f32(vq[k])));
-      for (int i = tid + 4 * T; i < n; i += T) m = fmaxf(m, fabsf(bf16_bits_to_f32(x[i])));
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    if ((tid & 63) == 0) sred[tid >> 6] = m;
-    __syncthreads();
-    for (int i = 0; i < T >> 6; ++i) m = fmaxf(m, sred[i]);
-    const float s0 = sold;
-    const float fresh = fmaxf(__fdiv_rn(m, 448.0f), 0x1p-126f);
-    const bool grow = slot > 0 && !(fresh <= s0);  // an unset (NaN) scale grows
-    s = (slot == 0 || grow) ? fresh : s0;
-    if (grow) {  // uniform
-      for (int c = tid; c < 256; c += T)
-        lut[c] = (uint8_t)f32_to_e4m3(__fdiv_rn(e4m3_to_f32((uint32_t)c) * s0, s));
-      __syncthreads();
-      requantise<IS_K>(page, lut, n, P, slot);
-      // V: the requantised pieces hold the slot the token goes to
-      if constexpr (!IS_K) __syncthreads();
-    }
-    if (tid == 0) scales[page_id] = s;
-  }
+  int slot;
+  const int64_t page_id = locate(p, b, slot);
+  if (page_id < 0) return;
+  uint8_t* page = pages + page_id * ((int64_t)n * P);
+  // Thread 0 reads the page's scale and publishes it in LDS before the
+  // reduction's barrier; it alone stores the new one, after it.
+  if (tid == 0) sold = slot > 0 ? scales[page_id] : 0.f;
+  float m = 0.f;
   if constexpr (IS_K) {
-    if (4 * tid < n) store_k<FP8>(page, P, slot, tid, kq, s);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) m = fmaxf(m, fabsf(kq.value(k)));
+    for (int i = tid + T; 4 * i < n; i += T) {
+      const Quad y{*(const u32x2*)(x + 4 * i)};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) m = fmaxf(m, fabsf(y.value(k)));
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) m = fmaxf(m, fabsf(bf16_bits_to_f32(vq[k])));
+    for (int i = tid + 4 * T; i < n; i += T) m = fmaxf(m, fabsf(bf16_bits_to_f32(x[i])));
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  if ((tid & 63) == 0) sred[tid >> 6] = m;
+  __syncthreads();
+  for (int i = 0; i < T >> 6; ++i) m = fmaxf(m, sred[i]);
+  const float s0 = sold;
+  const float fresh = fmaxf(__fdiv_rn(m, 448.0f), 0x1p-126f);
+  const bool grow = slot > 0 && !(fresh <= s0);  // an unset (NaN) scale grows
+  const float s = (slot == 0 || grow) ? fresh : s0;
+  if (grow) {  // uniform
+    for (int c = tid; c < 256; c += T)
+      lut[c] = (uint8_t)f32_to_e4m3(__fdiv_rn(e4m3_to_f32((uint32_t)c) * s0, s));
+    __syncthreads();
+    requantise<IS_K>(page, lut, n, P, slot);
+    // V: the requantised pieces hold the slot the token goes to
+    if constexpr (!IS_K) __syncthreads();
+  }
+  if (tid == 0) scales[page_id] = s;
+  if constexpr (IS_K) {
+    if (4 * tid < n) store_k(page, P, slot, tid, kq, s);
     for (int i = tid + T; 4 * i < n; i += T)
-      store_k<FP8>(page, P, slot, i, Quad{*(const u32x2*)(x + 4 * i)}, s);
+      store_k(page, P, slot, i, Quad{*(const u32x2*)(x + 4 * i)}, s);
   } else {
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (tid + k * T < n) store_v<FP8>(page, P, slot, tid + k * T, vq[k], s);
-    for (int i = tid + 4 * T; i < n; i += T) store_v<FP8>(page, P, slot, i, x[i], s);
+      if (tid + k * T < n) store_v(page, P, slot, tid + k * T, vq[k], s);
+    for (int i = tid + 4 * T; i < n; i += T) store_v(page, P, slot, i, x[i], s);
   }
 }
 
-template <bool FP8>
-__global__ __launch_bounds__(kAppendMaxThreads) void append_kernel(AppendParams p) {
+__global__ __launch_bounds__(kAppendMaxThreads) void append_fp8_kernel(AppendParams p) {
   if (blockIdx.y == 0)
-    append_side<FP8, true>(p, p.k_pages, p.k_scales, p.k_new);
+    append_side<true>(p, p.k_pages, p.k_scales, p.k_new);
   else
-    append_side<FP8, false>(p, p.v_pages, p.v_scales, p.v_new);
+    append_side<false>(p, p.v_pages, p.v_scales, p.v_new);
 }
 
-int append_threads(int num_kv_heads, int head_dim) {
-  const int quads = num_kv_heads * head_dim / 4;
-  const int t = (quads + 63) / 64 * 64;
-  return t > kAppendMaxThreads ? kAppendMaxThreads : t;
+// bf16: store chunk c (8 values) of the token's K and V.  K non-temporal, as above.
+__device__ __forceinline__ void store_chunk(uint8_t* __restrict__ kpage,
+                                            uint8_t* __restrict__ vpage, int P, int slot, int c,
+                                            u32x4 k, u32x4 v) {
+  __builtin_nontemporal_store(k, (u32x4*)(kpage + ((int64_t)c * P + slot) * 16));
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    *(uint16_t*)(vpage + ((int64_t)(8 * c + i) * P + slot) * 2) =
+        (uint16_t)(v[i >> 1] >> (16 * (i & 1)));
+}
+
+// bf16: one workgroup per sequence, thread i with chunk i of K and of V (of very wide
+// tokens every blockDim.x-th).  Nothing crosses the values, so the fewest waves that
+// hold the token are the fastest: with a workgroup for each side and twice the threads,
+// as for fp8, calls of up to 512 sequences took 4-17% longer than with the token loaded
+// after its page is known and plain stores, this way 8-14% less (512 sequences of 8
+// heads, four calls in a row, each over another pool: 45.6 us that way, 38.9 by two
+// workgroups, 36.0 so).
+__global__ __launch_bounds__(kAppendMaxThreads) void append_bf16_kernel(AppendParams p) {
+  const int b = blockIdx.x, c0 = threadIdx.x;
+  const int P = p.page_size, n = p.num_kv_heads * p.head_dim, chunks = n / 8;
+  const u32x4* k_new = (const u32x4*)(p.k_new + (int64_t)b * n);
+  const u32x4* v_new = (const u32x4*)(p.v_new + (int64_t)b * n);
+  u32x4 k{0u, 0u, 0u, 0u}, v{0u, 0u, 0u, 0u};
+  if (c0 < chunks) {
+    k = k_new[c0];
+    v = v_new[c0];
+  }
+  int slot;
+  const int64_t page_id = locate(p, b, slot);
+  if (page_id < 0) return;
+  uint8_t* kpage = p.k_pages + page_id * ((int64_t)n * P * 2);
+  uint8_t* vpage = p.v_pages + page_id * ((int64_t)n * P * 2);
+  if (c0 < chunks) store_chunk(kpage, vpage, P, slot, c0, k, v);
+  for (int c = c0 + blockDim.x; c < chunks; c += blockDim.x)
+    store_chunk(kpage, vpage, P, slot, c, k_new[c], v_new[c]);
+}
+
+// Threads (a multiple of 64) that hold `per` values of a token each.
+static dim3 append_threads(const AppendParams& p, int per) {
+  const int t = (p.num_kv_heads * p.head_dim / per + 63) / 64 * 64;
+  return dim3(t > kAppendMaxThreads ? kAppendMaxThreads : t);
 }
 
 hipError_t launch_append(const AppendParams& p, bool fp8, hipStream_t s) {
@@ -285,11 +301,10 @@ hipError_t launch_append(const AppendParams& p, bool fp8, hipStream_t s) {
     const hipError_t e = launch_fill_i32(p.dev_status, (int32_t)DORA_OK, 1, s);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid(p.num_seqs, 2), block(append_threads(p.num_kv_heads, p.head_dim));
   if (fp8)
-    hipLaunchKernelGGL(append_kernel<true>, grid, block, 0, s, p);
+    hipLaunchKernelGGL(append_fp8_kernel, dim3(p.num_seqs, 2), append_threads(p, 4), 0, s, p);
   else
-    hipLaunchKernelGGL(append_kernel<false>, grid, block, 0, s, p);
+    hipLaunchKernelGGL(append_bf16_kernel, dim3(p.num_seqs), append_threads(p, 8), 0, s, p);
   return hipGetLastError();
 }
 

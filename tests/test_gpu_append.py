@@ -272,3 +272,8 @@ def test_append_odd_and_very_wide_tokens(dt, Hkv, d, P):
     if dt == 1:
         assert np.array_equal(d_ks.cpu().numpy().view(np.uint32), hks.view(np.uint32))
         assert np.array_equal(d_vs.cpu().numpy().view(np.uint32), hvs.view(np.uint32))
+
+
+def test_append_bf16_tokens_wider_than_a_workgroup():
+    """More than 8,192 bf16 values a token: past what the workgroup's threads hold."""
+    test_append_odd_and_very_wide_tokens(dt=0, Hkv=70, d=128, P=16)
