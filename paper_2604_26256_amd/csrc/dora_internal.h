@@ -237,6 +237,7 @@ struct PackParams {
   float* vs_out;
   int32_t* dev_status;
   int32_t has_scales;
+  int32_t layer;          // pages per grid layer, set by the launch
   PackHeader hdr;
 };
 

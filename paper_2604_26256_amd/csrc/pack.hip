@@ -23,7 +23,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kCopyThreads = 256;
 constexpr int kCopyUnroll = 2;
 constexpr int kChunkBytes = kCopyThreads * kCopyUnroll * 16;  // 8 KiB
-constexpr int kGridPages = 32768;  // pages per grid layer
+constexpr int kGridPages = 32768;  // pages per grid layer, at most
 
 void make_pack_header(const dora_pack_desc& d, int64_t n_pages, PackHeader* h) {
   memset(h, 0, sizeof *h);
@@ -41,6 +41,10 @@ void make_pack_header(const dora_pack_desc& d, int64_t n_pages, PackHeader* h) {
   memcpy(p + 32, &n_pages, 8);
   memcpy(p + 40, &page_bytes, 8);
   v32 = d.n_seqs;         memcpy(p + 48, &v32, 4);
+}
+
+__host__ __device__ inline int chunks_per_page(const PackParams& p) {
+  return (int)((p.page_bytes + kChunkBytes - 1) / kChunkBytes);
 }
 
 // Copy `bytes` (multiple of 16) from src to dst, this workgroup's chunk only.
@@ -75,10 +79,10 @@ __device__ __forceinline__ void zero_chunk(uint8_t* __restrict__ dst, int64_t by
 // pages after the copies: with the above, 16,384 pages of 8 KiB, pack 147 -> 92
 // us, unpack 182 -> 101).
 __global__ __launch_bounds__(kCopyThreads) void pack_kernel(PackParams p) {
-  const int cpp = (int)gridDim.x / 2;
+  const int cpp = chunks_per_page(p);
   const int which = (int)blockIdx.x >= cpp ? 1 : 0;  // 0: K, 1: V
   const int c = (int)blockIdx.x - which * cpp;
-  const int64_t j = (int64_t)blockIdx.z * kGridPages + blockIdx.y;
+  const int64_t j = (int64_t)blockIdx.z * p.layer + blockIdx.y;
   const bool first = blockIdx.x == 0 && j == 0;
   uint8_t* body = p.packed + 256;
   if (first && threadIdx.x < 64)
@@ -104,6 +108,9 @@ __global__ __launch_bounds__(kCopyThreads) void pack_kernel(PackParams p) {
 // Every workgroup checks the header first; on any mismatch nothing is written
 // and the first workgroup reports the status.
 __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(PackParams p) {
+  const int64_t j = (int64_t)blockIdx.z * p.layer + blockIdx.y;
+  const bool first = blockIdx.x == 0 && j == 0;
+  if (j >= p.n_pages && !first) return;
   __shared__ int bad;
   if (threadIdx.x == 0) bad = 0;
   __syncthreads();
@@ -115,11 +122,9 @@ __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(PackParams p) {
     }
   }
   __syncthreads();
-  const int cpp = (int)gridDim.x / 2;
+  const int cpp = chunks_per_page(p);
   const int which = (int)blockIdx.x >= cpp ? 1 : 0;  // 0: K, 1: V
   const int c = (int)blockIdx.x - which * cpp;
-  const int64_t j = (int64_t)blockIdx.z * kGridPages + blockIdx.y;
-  const bool first = blockIdx.x == 0 && j == 0;
   if (first && threadIdx.x == 0 && p.dev_status)
     *p.dev_status = !bad      ? (int32_t)DORA_OK
                     : bad & 1 ? (int32_t)DORA_ERR_INVALID_ARG
@@ -139,19 +144,26 @@ __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(PackParams p) {
   copy_chunk(dst, src, bytes);
 }
 
-static dim3 copy_grid(const PackParams& p) {
-  const int64_t cpp = (p.page_bytes + kChunkBytes - 1) / kChunkBytes;
-  const int64_t y = p.n_pages < kGridPages ? (p.n_pages > 0 ? p.n_pages : 1) : kGridPages;
-  return dim3((unsigned)(2 * cpp), (unsigned)y, (unsigned)((p.n_pages + y - 1) / y + (p.n_pages == 0)));
+// The copy's grid; sets p.layer (from the arguments both it and the chunks of a page
+// are known sooner than from the grid's own dimensions).
+static dim3 copy_grid(PackParams& p) {
+  const int64_t n = p.n_pages > 0 ? p.n_pages : 1;
+  const int64_t z = (n + kGridPages - 1) / kGridPages;
+  p.layer = (int32_t)((n + z - 1) / z);
+  return dim3((unsigned)(2 * chunks_per_page(p)), (unsigned)p.layer, (unsigned)z);
 }
 
-hipError_t launch_pack(const PackParams& p, hipStream_t s) {
-  hipLaunchKernelGGL(pack_kernel, copy_grid(p), dim3(kCopyThreads), 0, s, p);
+hipError_t launch_pack(const PackParams& params, hipStream_t s) {
+  PackParams p = params;
+  const dim3 grid = copy_grid(p);
+  hipLaunchKernelGGL(pack_kernel, grid, dim3(kCopyThreads), 0, s, p);
   return hipGetLastError();
 }
 
-hipError_t launch_unpack(const PackParams& p, hipStream_t s) {
-  hipLaunchKernelGGL(unpack_kernel, copy_grid(p), dim3(kCopyThreads), 0, s, p);
+hipError_t launch_unpack(const PackParams& params, hipStream_t s) {
+  PackParams p = params;
+  const dim3 grid = copy_grid(p);
+  hipLaunchKernelGGL(unpack_kernel, grid, dim3(kCopyThreads), 0, s, p);
   return hipGetLastError();
 }
 

@@ -390,3 +390,11 @@ def test_pack_unpack_grid_edges(dt, Hkv, d, P, n):
     assert torch.equal(k2b, want_k) and torch.equal(v2b, want_v)
     if dt:
         assert torch.equal(ks2, want_ks) and torch.equal(vs2, want_vs)
+
+
+@pytest.mark.parametrize("dt,Hkv,d,P,n", [
+    (1, 1, 64, 16, 65537),     # three layers of 21,846 pages, the last not full
+])
+def test_pack_unpack_three_layers(dt, Hkv, d, P, n):
+    """Page counts past two layers of the grid."""
+    test_pack_unpack_grid_edges(dt=dt, Hkv=Hkv, d=d, P=P, n=n)
