@@ -5,11 +5,15 @@
 //
 // Both kernels are HBM-bound streaming copies: each workgroup moves one 8 KiB
 // chunk of one page (K or V) with 16-byte loads, all loads issued before the
-// stores.  Every byte is read and written once, so both are non-temporal.  Pack
-// and unpack of 1 GiB one way (32 KiB pages) 828 -> 775 us, of 64 MiB 52 -> 50,
-// to and from pinned host memory level (54 and 56 GB/s); with 16 KiB chunks 789
-// and 53 us, with 4 KiB 776 and 54; only the loads or only the stores
-// non-temporal 817 and 799 us at 1 GiB.
+// stores.  Every byte is read once, so the loads are non-temporal.  The stores are
+// too, except where what is written and what it is written from fit the 256 MB
+// last-level cache about once (32 to 300 MB one way) and are more than the L2s hold:
+// there plain stores leave the packed buffer for the unpack.  Pack and unpack, 32 KiB
+// pages, over new buffers each time / over the same ones, plain loads and stores in
+// 16 KiB chunks, all non-temporal, non-temporal loads: 16 MB one way 17.0 / 13.4 us,
+// 15.7 / 11.4, 15.2 / 12.8; 64 MB 49.7 / 39.6, 48.2 / 46.0, 46.6 / 43.4; 192 MB 151 /
+// 150, 135 / 134, 128 / 120; 512 MB 392 / 394, 360 / 358, 390 / 389.  To and from pinned
+// host memory level (54 and 56 GB/s).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -48,6 +52,7 @@ __host__ __device__ inline int chunks_per_page(const PackParams& p) {
 }
 
 // Copy `bytes` (multiple of 16) from src to dst, this workgroup's chunk only.
+template <bool NT>
 __device__ __forceinline__ void copy_chunk(uint8_t* __restrict__ dst,
                                            const uint8_t* __restrict__ src, int64_t bytes) {
   u32x4 r[kCopyUnroll];
@@ -59,7 +64,12 @@ __device__ __forceinline__ void copy_chunk(uint8_t* __restrict__ dst,
 #pragma unroll
   for (int i = 0; i < kCopyUnroll; ++i) {
     const int64_t o = ((int64_t)i * kCopyThreads + threadIdx.x) * 16;
-    if (o < bytes) __builtin_nontemporal_store(r[i], (u32x4*)(dst + o));
+    if (o < bytes) {
+      if constexpr (NT)
+        __builtin_nontemporal_store(r[i], (u32x4*)(dst + o));
+      else
+        *(u32x4*)(dst + o) = r[i];
+    }
   }
 }
 
@@ -78,6 +88,7 @@ __device__ __forceinline__ void zero_chunk(uint8_t* __restrict__ dst, int64_t by
 // workgroup of its own, the last one, the scales took two dependent loads per 256
 // pages after the copies: with the above, 16,384 pages of 8 KiB, pack 147 -> 92
 // us, unpack 182 -> 101).
+template <bool NT>
 __global__ __launch_bounds__(kCopyThreads) void pack_kernel(PackParams p) {
   const int cpp = chunks_per_page(p);
   const int which = (int)blockIdx.x >= cpp ? 1 : 0;  // 0: K, 1: V
@@ -102,11 +113,12 @@ __global__ __launch_bounds__(kCopyThreads) void pack_kernel(PackParams p) {
     return;
   }
   const uint8_t* src = (which ? p.v_pages : p.k_pages) + (int64_t)pid * p.page_bytes + off;
-  copy_chunk(dst, src, bytes);
+  copy_chunk<NT>(dst, src, bytes);
 }
 
 // Every workgroup checks the header first; on any mismatch nothing is written
 // and the first workgroup reports the status.
+template <bool NT>
 __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(PackParams p) {
   const int64_t j = (int64_t)blockIdx.z * p.layer + blockIdx.y;
   const bool first = blockIdx.x == 0 && j == 0;
@@ -141,7 +153,7 @@ __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(PackParams p) {
   }
   const uint8_t* src = body + ((int64_t)which * p.n_pages + j) * p.page_bytes + off;
   uint8_t* dst = (which ? p.v_out : p.k_out) + (int64_t)pid * p.page_bytes + off;
-  copy_chunk(dst, src, bytes);
+  copy_chunk<NT>(dst, src, bytes);
 }
 
 // The copy's grid; sets p.layer (from the arguments both it and the chunks of a page
@@ -153,17 +165,29 @@ static dim3 copy_grid(PackParams& p) {
   return dim3((unsigned)(2 * chunks_per_page(p)), (unsigned)p.layer, (unsigned)z);
 }
 
+// Whether the stores are non-temporal (the figures are at the top).
+static bool nt_stores(const PackParams& p) {
+  const int64_t one_way = 2 * p.n_pages * p.page_bytes;
+  return one_way <= 32000000 || one_way > 300000000;
+}
+
 hipError_t launch_pack(const PackParams& params, hipStream_t s) {
   PackParams p = params;
   const dim3 grid = copy_grid(p);
-  hipLaunchKernelGGL(pack_kernel, grid, dim3(kCopyThreads), 0, s, p);
+  if (nt_stores(p))
+    hipLaunchKernelGGL(pack_kernel<true>, grid, dim3(kCopyThreads), 0, s, p);
+  else
+    hipLaunchKernelGGL(pack_kernel<false>, grid, dim3(kCopyThreads), 0, s, p);
   return hipGetLastError();
 }
 
 hipError_t launch_unpack(const PackParams& params, hipStream_t s) {
   PackParams p = params;
   const dim3 grid = copy_grid(p);
-  hipLaunchKernelGGL(unpack_kernel, grid, dim3(kCopyThreads), 0, s, p);
+  if (nt_stores(p))
+    hipLaunchKernelGGL(unpack_kernel<true>, grid, dim3(kCopyThreads), 0, s, p);
+  else
+    hipLaunchKernelGGL(unpack_kernel<false>, grid, dim3(kCopyThreads), 0, s, p);
   return hipGetLastError();
 }
 

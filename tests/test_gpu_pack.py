@@ -394,7 +394,12 @@ def test_pack_unpack_grid_edges(dt, Hkv, d, P, n):
 
 @pytest.mark.parametrize("dt,Hkv,d,P,n", [
     (1, 1, 64, 16, 65537),     # three layers of 21,846 pages, the last not full
+    (0, 8, 128, 16, 488),      # up to 32 MB one way: non-temporal stores ...
+    (0, 8, 128, 16, 489),      # ... plain ones past it ...
+    (0, 8, 128, 16, 4577),     # ... up to 300 MB
+    (0, 8, 128, 16, 4578),
 ])
-def test_pack_unpack_three_layers(dt, Hkv, d, P, n):
-    """Page counts past two layers of the grid."""
+def test_pack_unpack_layers_and_store_kinds(dt, Hkv, d, P, n):
+    """Page counts past two layers of the grid, and either side of the sizes where the
+    kind of store changes."""
     test_pack_unpack_grid_edges(dt=dt, Hkv=Hkv, d=d, P=P, n=n)
