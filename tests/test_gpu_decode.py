@@ -335,3 +335,55 @@ def test_segment_kernel_many_chunks(dt, d, P, Hkv, G, lens):
     assert torch.equal(run_decode(b), out)
     cut = run_decode(b, min_range_pages=8)
     assert (out.float() - cut.float()).abs().max().item() <= TOL[dt] / 2
+
+
+# ---------------------------------------------------------------------------
+# the stream-K decode: the default call of small batches runs the segment kernel,
+# so these name the default stream-K cut (min_range_pages = 8) themselves
+# ---------------------------------------------------------------------------
+
+STREAM_K = {"min_range_pages": 8}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("P", [16, 32])
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("G", [1, 4, 7, 16])
+def test_stream_k_ragged_lengths(d, P, dt, G):
+    print(f"[case] stream-K shapes d={d} P={P} dt={dt} G={G}", flush=True)
+    Hkv = 2
+    lens = np.array(RAGGED, np.int32)
+    w = _w(B=len(lens), Hq=G * Hkv, Hkv=Hkv, d=d, P=P, dt=dt, lens=lens)
+    b = gpu_batch(w, lengths=lens, seed_index=100 + d + P + dt + G)
+    assert segment_pages(b) > 0 and segment_pages(b, **STREAM_K) == 0
+    out = run_decode(b, out=torch.full_like(b.q, float("nan")), **STREAM_K)
+    assert max_abs_err(out, oracle_for(b)) <= TOL[dt]
+    assert torch.all(out[0] == 0), "empty sequence must give zeros"
+    assert torch.equal(run_decode(b, **STREAM_K), out)
+
+
+def test_stream_k_cuts_are_deterministic_bitwise():
+    lens = np.array([3000, 17, 900, 4000, 1], np.int32)
+    w = _w(B=len(lens), Hq=28, Hkv=4, d=128, P=16, dt=0, lens=lens)
+    b = gpu_batch(w, lengths=lens, seed_index=9)
+    assert cut_segments(lens, 16, b.stride, 4, decode_waves(b, **STREAM_K))
+    a = run_decode(b, **STREAM_K).clone()
+    for _ in range(3):
+        assert torch.equal(run_decode(b, **STREAM_K), a)
+    assert max_abs_err(a, oracle_for(b)) <= TOL[0]
+
+
+@pytest.mark.parametrize("long_row", [0, 20000])
+def test_stream_k_batch_larger_than_one_launch(long_row):
+    """More sequences than one launch takes (8192), by stream-K: cut records per
+    wavefront, in both launches; with a long row in the second."""
+    rng = np.random.default_rng(3)
+    lens = rng.integers(0, 40, 9000).astype(np.int32)
+    if long_row:
+        lens[8500] = long_row
+    w = _w(B=len(lens), Hq=8, Hkv=2, d=64, P=16, dt=0, lens=lens)
+    b = gpu_batch(w, lengths=lens, seed_index=14)
+    out = run_decode(b, out=torch.full_like(b.q, float("nan")), **STREAM_K)
+    seqs = [0, 1, 8190, 8191, 8192, 8193, 8500, 8999] + [int(i) for i in rng.choice(9000, 20)]
+    seqs = sorted(set(seqs))
+    assert max_abs_err(out, oracle_for(b, seqs), seqs) <= TOL[0]

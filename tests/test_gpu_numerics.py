@@ -89,8 +89,9 @@ def test_zero_query_is_the_mean_of_values(dt, P):
 def test_one_sequence_of_half_a_million_tokens(dt, P):
     """The geometry's far corner: one sequence of 2^19 tokens (2^15 or 2^14
     pages in one block-table row) over the widest query group (G = 16) of a
-    single KV head, so the one segment is cut across every wavefront of the
-    default launch and the combine merges over a thousand pieces.  A softmax
+    single KV head, by the default call (fp8: 1,024 chunks of 512 tokens) and by
+    stream-K, which cuts the one segment across every wavefront, so that the
+    combine merges about a thousand pieces either way.  A softmax
     scale of 1 keeps the output dominated by a few tokens (with 1/sqrt(d) the
     output of half a million random values would be near zero and say
     little).  The oracle takes about ten seconds per case."""
@@ -99,11 +100,11 @@ def test_one_sequence_of_half_a_million_tokens(dt, P):
     pages = int(wl.pages_needed(lens, P).sum()) + 8
     w = wl.Workload("m", 1, 16, 1, 64, P, dt, pages, "uniform", lo=1, hi=1)
     b = gpu_batch(w, lengths=lens, seed_index=330 + dt)
-    out = run_decode(b, sm_scale=1.0)
     ref = _oracle(b, 1.0)
     assert np.abs(ref).max() > 0.5, "the check needs outputs of order one"
-    err = max_abs_err(out, ref)
-    assert err <= TOL[dt], err
+    for cut in ({}, {"min_range_pages": 8}):
+        err = max_abs_err(run_decode(b, sm_scale=1.0, **cut), ref)
+        assert err <= TOL[dt], (cut, err)
 
 
 def test_widest_kv_head_count():
@@ -152,3 +153,21 @@ def test_pages_of_minus_infinity_scores(d, P, dt):
     for cut in ({}, {"min_range_pages": 8}, {"num_waves": 50, "min_range_pages": 1}):
         err = max_abs_err(run_decode(b, **cut), ref)
         assert err <= TOL[dt], (cut, err)
+
+
+@pytest.mark.parametrize("dt,P", [(0, 16), (1, 32)])
+@pytest.mark.parametrize("case", ["scale", "large", "zero"])
+def test_stream_k_scales_and_scores(dt, P, case):
+    """A caller's softmax scale, scores of a few hundred and a zero query, by the
+    stream-K cut (the default call runs these batches per segment)."""
+    print(f"[case] stream-K {case} dt={dt} P={P}", flush=True)
+    b = gpu_batch(_w(128, P, dt), lengths=LENS, seed_index=360 + dt)
+    scale = 1.0 if case == "scale" else 0.0
+    if case == "large":
+        b.q.copy_((b.q.float() * 24).to(torch.bfloat16))
+    elif case == "zero":
+        b.q.zero_()
+    ref = _oracle(b, scale)
+    out = run_decode(b, sm_scale=scale, min_range_pages=8)
+    assert max_abs_err(out, ref) <= TOL[dt]
+    assert max_abs_err(run_decode(b, sm_scale=scale), ref) <= TOL[dt]

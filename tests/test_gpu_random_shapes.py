@@ -62,6 +62,13 @@ def test_random_geometries_match_the_oracle():
                                         v_scales=b.v_scales)
             torch.cuda.synchronize()
             assert (og.float() - out.float()).abs().max().item() <= TOL[dt], case
+            det = torch.full((B // 2,), -1, dtype=torch.int32, device="cuda")
+            d_.dora_decode_attn_grouped(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens,
+                                        b.version_ids, og, group_size=2, num_kv_heads=Hkv,
+                                        page_size=P, kv_dtype=dt, k_scales=b.k_scales,
+                                        v_scales=b.v_scales, shared_pages_out=det)
+            assert not det.any(), case
+            assert (og.float() - out.float()).abs().max().item() <= TOL[dt], case
 
 
 def test_random_scales_ranges_and_prepared_calls():
@@ -119,13 +126,24 @@ def test_random_grpo_batches_grouped_match_the_oracle():
               f"prompts [{lo}, {hi}]", flush=True)
         w = wl.Workload("g", B, G * Hkv, Hkv, d, P, dt, B * ((hi + 2000) // P + 2) + 64,
                         "lognormal", 300, 1.0, 1, 2000)
-        b, _ = wl.make_grpo_batch(w, group_size=M, prompt_range=(lo, hi), device="cuda",
-                                  seed_index=5000 + case)
+        b, shared = wl.make_grpo_batch(w, group_size=M, prompt_range=(lo, hi), device="cuda",
+                                       seed_index=5000 + case)
         og = torch.empty_like(b.q)
         d_.dora_decode_attn_grouped(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens,
                                     b.version_ids, og, group_size=M, num_kv_heads=Hkv,
                                     page_size=P, kv_dtype=dt, k_scales=b.k_scales,
                                     v_scales=b.v_scales)
         torch.cuda.synchronize()
-        err = max_abs_err(og, oracle_for(b))
+        ref = oracle_for(b)
+        err = max_abs_err(og, ref)
+        assert err <= TOL[dt], (case, err)
+        # most of these batches are small and ran as the plain decode: with the
+        # counts asked for the prefix kernel and the suffix decode run
+        det = torch.full((B // M,), -1, dtype=torch.int32, device="cuda")
+        d_.dora_decode_attn_grouped(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens,
+                                    b.version_ids, og, group_size=M, num_kv_heads=Hkv,
+                                    page_size=P, kv_dtype=dt, k_scales=b.k_scales,
+                                    v_scales=b.v_scales, shared_pages_out=det)
+        assert det.tolist() == shared[::M].tolist(), case
+        err = max_abs_err(og, ref)
         assert err <= TOL[dt], (case, err)
