@@ -1,5 +1,5 @@
 // Device building blocks of the decode-attention kernels, shared by the
-// stream-K decode kernel and the group-prefix kernel: the register image of
+// stream-K decode, segment and group-prefix kernels: the register image of
 // one (page, KV head) tile, its loads, the per-page MFMA + online-softmax
 // step and the query operand.  Included by HIP sources only.
 #pragma once
@@ -164,7 +164,10 @@ __device__ __forceinline__ void load_step(PageRegs<D, T, FP8>& r, const uint8_t*
 // feeds NC MFMAs); tile c has its own query operand, accumulator and running
 // max / sum.  `r` holds the page as each lane loaded it (from HBM or LDS);
 // nvalid tokens of the page count; ksc folds the softmax scale (and the fp8 K
-// page scale), vsc the fp8 V page scale.
+// page scale), vsc the fp8 V page scale.  Every caller has one tile; without the
+// parameter the compiler schedules the segment kernel differently, and 512-token
+// chunks of long 16-token rows get slower (4 bf16 rows of 2 KV heads, one of 39,840
+// tokens: 19.7 -> 24.9 us).
 template <int D, int P, bool FP8, int NC>
 __device__ __forceinline__ void consume_page_tiles(const PageRegs<D, P, FP8>& r, int nvalid,
                                                    float ksc, float vsc,
