@@ -3,7 +3,8 @@
     python bench.py [--steps K] [--warmup W] [--workload NAME] [--only-main]
                     [--no-cpu-baseline] [--no-flush] [--gpus 1]
 
-One step = one dora_decode_attn call (stream-K decode kernel + combine) over
+One step = one dora_decode_attn call (stream-K decode kernel + combine, or the
+segment kernel where the call takes that route) over
 one synthetic long-tailed decode batch whose inputs are already resident in
 HBM.  Caches (256 MB Infinity Cache, 8 x 4 MB L2) are evicted by a 1 GiB read
 before every step, outside the timed events.  The main line is the largest
@@ -17,7 +18,7 @@ sequence advances one token per step).  roofline: the decode kernel's
 algorithmic bytes (K and V of valid tokens, page scales, Q, output, block
 table and lengths) over its average duration, measured with HIP events that
 the library records around each kernel on the launch stream
-(dora_decode_attn_timed).  Two achievable-bandwidth references stand beside
+(dora_decode_attn_timed); kernel names the one that ran.  Two achievable-bandwidth references stand beside
 the 8 TB/s peak, both read by the library's own streaming-read kernel
 (dora_stream_read, 16-byte non-temporal loads): random 4 KiB tiles of a
 16 GiB buffer (achievable_gbps), and each batch's own tile sequence in its
@@ -76,8 +77,10 @@ COMPUTE_PASSES = {
 }
 COMPUTE_CMD = ("cd /tmp && timeout -s KILL 300 rocprofv3 --pmc {c} --output-format csv "
                "-d $REPO/gpurun_out/pmc_{p}_{w} -o run -- python $REPO/bench.py {args}")
+# Every kernel that a summary under profiles/ names, and the rules that launch them.
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2604_26256_amd", "csrc", f)
-                  for f in ("decode.hip", "decode_core.h", "dora_internal.h", "api.cpp")]
+                  for f in ("decode.hip", "segment.hip", "grouped.hip", "append.hip", "pack.hip",
+                            "decode_core.h", "merge_core.h", "dora_internal.h", "api.cpp")]
 
 
 def _code_only(text: str) -> str:
@@ -91,8 +94,8 @@ def _code_only(text: str) -> str:
 
 
 def kernel_source_hash() -> str:
-    """Hash of the code (not the comments) of the sources the decode kernel's
-    launches are built from; stored with every counter summary."""
+    """Hash of the code (not the comments) of the sources the profiled kernels
+    are built from; stored with every counter summary and trace."""
     h = hashlib.sha256()
     for f in KERNEL_SOURCES:
         with open(f, encoding="utf-8") as fh:
@@ -184,12 +187,14 @@ def summarize_trace(d, workload, grpo=False):
     print(out)
 
 
-def _kernel_instance(w):
-    """Pattern of the decode kernel's template instance that workload w
-    launches (head dim, page size, fp8 or not, the page-buffer count the
-    library picks for that geometry, plain rather than suffix decode)."""
-    return (rf"decode_kernel<{w.head_dim}, {w.page_size}, "
-            rf"{'true' if w.kv_dtype == 1 else 'false'}, \d+, false>")
+def _kernel_instance(w, kernel="decode_kernel"):
+    """Pattern of the template instance that workload w launches: head dim, page
+    size, fp8 or not, then the page-buffer count the library picks for that
+    geometry and plain rather than suffix decode (decode_kernel), or the steps'
+    tokens (segment_kernel)."""
+    return (rf"{kernel}<{w.head_dim}, {w.page_size}, "
+            rf"{'true' if w.kv_dtype == 1 else 'false'}, \d+"
+            rf"{', false' if kernel == 'decode_kernel' else ''}>")
 
 
 def summarize_bench_trace(d, line_path):
@@ -209,7 +214,8 @@ def summarize_bench_trace(d, line_path):
     by_inst = {}
     for w in wl.WORKLOADS:
         if w.name in line.get("workloads", {}):
-            by_inst.setdefault(_kernel_instance(w), []).append(w.name)
+            kernel = line["workloads"][w.name]["roofline"].get("kernel", "decode_kernel")
+            by_inst.setdefault(_kernel_instance(w, kernel), []).append(w.name)
     shared_with_grpo = set()
     if "shared_prefix" in line:       # the GRPO batch's plain decode, timed as a whole call
         shared_with_grpo.add(_kernel_instance(wl.GRPO_WORKLOAD))
@@ -514,8 +520,12 @@ def time_decode(torch, dora, b, steps, warmup, flush, num_waves=0):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     step_ms = np.array([s.elapsed_time(e) for s, e in zip(starts, ends)])
-    # (b) per kernel: the library records events before the decode kernel,
-    # between it and the combine kernel, and after the combine kernel
+    # (b) per kernel: the library records events before the decode (or segment)
+    # kernel, after it, and after the combine, where the batch's route has one
+    pages = dora.dora_decode_segment_pages(dora.make_decode_desc(
+        num_seqs=w.num_seqs, num_q_heads=w.num_q_heads, num_kv_heads=w.num_kv_heads,
+        head_dim=w.head_dim, page_size=w.page_size, block_table_stride=b.stride,
+        num_pages=w.num_pages, kv_dtype=w.kv_dtype, num_waves=num_waves))
     ev = make_events(torch, 3)
     handles = [e.cuda_event for e in ev]
     split, comb = [], []
@@ -526,7 +536,8 @@ def time_decode(torch, dora, b, steps, warmup, flush, num_waves=0):
         split.append(ev[0].elapsed_time(ev[1]))
         comb.append(ev[1].elapsed_time(ev[2]))
     return {"step_ms": step_ms, "wall_s": wall, "split_ms": np.array(split),
-            "combine_ms": np.array(comb), "out": out}
+            "kernel": "segment_kernel" if pages else "decode_kernel",
+            "combine_ms": None if pages >= b.stride else np.array(comb), "out": out}
 
 
 def decode_record(w, lengths, t):
@@ -543,7 +554,8 @@ def decode_record(w, lengths, t):
         "hbm_frac_of_peak": ab["total"] / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
         "split_kernel_ms": split_ms,
         "split_kernel_gbps": ab["total"] / (split_ms * 1e-3) / 1e9,
-        "combine_ms": float(np.mean(t["combine_ms"])),
+        "kernel": t.get("kernel", "decode_kernel"),
+        "combine_ms": float(np.mean(t["combine_ms"])) if t["combine_ms"] is not None else None,
         "algorithmic_bytes": ab,
         "lengths": {k: (round(v, 3) if isinstance(v, float) else v) for k, v in st.items()},
     }
@@ -852,7 +864,7 @@ def roofline_of(rec, achievable_gbps):
     pat = rec.get("pattern_reference")
     return {
         "bound": "hbm",
-        "kernel": "decode_kernel",
+        "kernel": rec.get("kernel", "decode_kernel"),
         "achieved": gbps,
         "peak": HBM_PEAK_GBPS,
         "unit": "GB/s",

@@ -3,8 +3,7 @@
  *
  * They are not part of the method.  They let a benchmark time the kernels of
  * one decode call separately, tell which ones they are, and compare the decode
- * kernel with a plain
- * streaming read that has the decode kernel's access pattern (random 4 KiB
+ * kernel with a plain streaming read that has its access pattern (random 4 KiB
  * tiles, 16-byte non-temporal loads): the achievable-bandwidth reference next
  * to the HBM peak in the decode kernel's roofline.  The conventions of dora.h
  * hold here too (caller-owned device memory, errors before any launch,

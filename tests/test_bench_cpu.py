@@ -10,6 +10,7 @@ kernel sources it was taken on."""
 import csv
 import json
 import os
+import re
 
 import numpy as np
 import pytest
@@ -240,3 +241,34 @@ def test_counter_summaries_are_used_only_on_matching_sources(tmp_path, monkeypat
     assert bench.load_pmc(w) is None
     os.remove(path)
     assert bench.load_pmc(w) is None
+
+
+def test_source_hash_covers_every_profiled_kernel():
+    """Every source that holds a kernel counts, but for the measurement and the
+    no-allocation helpers, which no summary backs; so do the headers they
+    include."""
+    csrc = os.path.join(bench.ROOT, "paper_2604_26256_amd", "csrc")
+    want = {"api.cpp"}
+    for f in os.listdir(csrc):
+        if f.endswith(".h") or (f.endswith(".hip") and f not in ("measure.hip", "noalloc.hip")):
+            want.add(f)
+    assert {os.path.basename(f) for f in bench.KERNEL_SOURCES} == want
+
+
+def test_record_names_the_kernel_that_ran():
+    """A batch whose segments run whole has no combine to report, and the
+    roofline and the trace summary name the segment kernel."""
+    w = wl.BY_NAME["tiny"]
+    lengths = wl.sample_lengths(w, wl.seeds(0)[0])
+    t = {"step_ms": np.array([0.007]), "split_ms": np.array([0.006]), "combine_ms": None,
+         "kernel": "segment_kernel"}
+    r = bench.decode_record(w, lengths, t)
+    assert r["kernel"] == "segment_kernel" and r["combine_ms"] is None
+    r.update(split_kernel_traffic_bytes=None, split_kernel_l2_hit_rate=None)
+    assert bench.roofline_of(r, 6_500.0)["kernel"] == "segment_kernel"
+    w = wl.BY_NAME["moe_fp8"]
+    names = ("void dora::segment_kernel<128, 32, true, 32>(dora::SegmentParams)",
+             "void dora::decode_kernel<128, 32, true, 2, false>(dora::DecodeParams)")
+    for kernel, name in zip(("segment_kernel", "decode_kernel"), names):
+        assert [bool(re.search(bench._kernel_instance(w, kernel), n)) for n in names] == \
+            [n is name for n in names]
