@@ -117,12 +117,11 @@ __global__ __launch_bounds__(kCopyThreads) void pack_kernel(PackParams p) {
 }
 
 // Every workgroup checks the header first; on any mismatch nothing is written
-// and the first workgroup reports the status.
+// and the first workgroup reports the status.  (Workgroups past the last page, fewer
+// pages' than the grid has layers, read it too: an exit before it costs the others
+// 0.3% at 475 MB.)
 template <bool NT>
 __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(PackParams p) {
-  const int64_t j = (int64_t)blockIdx.z * p.layer + blockIdx.y;
-  const bool first = blockIdx.x == 0 && j == 0;
-  if (j >= p.n_pages && !first) return;
   __shared__ int bad;
   if (threadIdx.x == 0) bad = 0;
   __syncthreads();
@@ -137,6 +136,8 @@ __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(PackParams p) {
   const int cpp = chunks_per_page(p);
   const int which = (int)blockIdx.x >= cpp ? 1 : 0;  // 0: K, 1: V
   const int c = (int)blockIdx.x - which * cpp;
+  const int64_t j = (int64_t)blockIdx.z * p.layer + blockIdx.y;
+  const bool first = blockIdx.x == 0 && j == 0;
   if (first && threadIdx.x == 0 && p.dev_status)
     *p.dev_status = !bad      ? (int32_t)DORA_OK
                     : bad & 1 ? (int32_t)DORA_ERR_INVALID_ARG
