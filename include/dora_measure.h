@@ -39,11 +39,6 @@ dora_status dora_decode_attn_timed(const dora_decode_desc* desc,
  * and for an invalid or unsupported descriptor or an empty batch. */
 int32_t dora_decode_segment_pages(const dora_decode_desc* desc);
 
-/* 1 where dora_decode_attn_grouped with shared_pages_out NULL runs as the plain
- * decode of the batch, 0 where it reads shared pages once (as it always does for a
- * caller that asks for the counts), and for an invalid descriptor or no batch. */
-int32_t dora_decode_grouped_as_plain(const dora_decode_desc* desc);
-
 /* Streaming-read reference kernel.  Reads n_tiles tiles of tile_bytes bytes,
  * tile i starting at base + tiles[i] * tile_bytes, with 16-byte non-temporal
  * loads.  `waves` one-wavefront workgroups each take an equal contiguous range

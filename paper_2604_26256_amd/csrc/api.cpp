@@ -113,22 +113,19 @@ int segment_split(const dora_decode_desc& d, int64_t segs, int64_t waves) {
 }
 
 // Whether a grouped call whose caller does not ask for the shared page counts
-// runs as the plain decode: where that takes the segment kernel, and the rows that
-// the tables can hold fit the 256 MB last-level cache.  The members' copies of a
-// prompt then come out of the caches, while the grouped call adds detection, prefix
-// partials and a suffix stream-K that cost 20-40 us however little there is to
-// do.  Grouped over plain, 22,239 random batches that the segment kernel takes
-// (2-128 members, prompts of 16-16,384 tokens, 8-4,096 tokens of response at the
-// median): 256-token chunks 2.4x (the worst 1.00), 512-token chunks 1.8x (11 of 3,776
-// below 0.97, the worst 0.90), whole segments up to 1,024 of them 3.4x within 256
-// MB (none below 0.98) and 1.4x past it, but 16 of 198 below 0.97 there, the worst 0.71.
+// runs as the plain decode: where that takes the segment kernel.  The members'
+// copies of a prompt then mostly come out of the caches, while the grouped call
+// adds detection, prefix partials and a suffix stream-K that cost 20-40 us
+// however little there is to do.  Grouped over plain, 5,000 random batches of
+// the lines above (2-16 members, prompts of 64-5,000 tokens, 64-2,048 tokens of
+// response at the median): 256-token chunks 2.2-2.9x (the worst 1.2x), 512-token
+// chunks 1.5-2.3x (0.95x), whole segments 1.4-4x up to 1,024 of them (0.99x);
+// beyond, 1.1-1.4x but 0.82x where the prompts are the bulk of the context.
 bool grouped_as_plain(const dora_decode_desc& d, int64_t waves) {
   const int64_t segs = (int64_t)d.num_seqs * d.num_kv_heads;
   if (segs > 2048) return false;
-  const int64_t row = (int64_t)d.block_table_stride * d.page_size * d.head_dim *
-                      (d.kv_dtype == DORA_KV_BF16 ? 4 : 2);  // K and V
   const int pages = segment_split(d, segs, waves);
-  return pages > 0 && (pages < d.block_table_stride || (segs <= 1024 && segs * row <= 256 << 20));
+  return pages > 0 && (pages < d.block_table_stride || segs <= 1024);
 }
 
 int min_range_of(const dora_decode_desc& d) {
@@ -220,11 +217,6 @@ int32_t dora_decode_segment_pages(const dora_decode_desc* desc) {
   if (check_desc(desc) != DORA_OK || desc->num_seqs == 0) return 0;
   const int64_t seqs = desc->num_seqs < kMaxSeqsPerLaunch ? desc->num_seqs : kMaxSeqsPerLaunch;
   return segment_split(*desc, seqs * desc->num_kv_heads, decode_waves(*desc));
-}
-
-int32_t dora_decode_grouped_as_plain(const dora_decode_desc* desc) {
-  if (check_desc(desc) != DORA_OK || desc->num_seqs == 0) return 0;
-  return grouped_as_plain(*desc, decode_waves(*desc));
 }
 
 }  // extern "C"

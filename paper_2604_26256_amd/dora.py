@@ -78,8 +78,6 @@ _lib.dora_decode_num_waves.argtypes = [_DescP]
 _lib.dora_decode_num_waves.restype = _I64
 _lib.dora_decode_segment_pages.argtypes = [_DescP]
 _lib.dora_decode_segment_pages.restype = _I32
-_lib.dora_decode_grouped_as_plain.argtypes = [_DescP]
-_lib.dora_decode_grouped_as_plain.restype = _I32
 _lib.dora_decode_attn_timed.argtypes = [_DescP, _P, _P, _P, _P, _P, _P, _P, _P, _SZ, _P, _P]
 _lib.dora_decode_attn_timed.restype = ctypes.c_int
 _lib.dora_stream_read.argtypes = [_P, _I64, _P, _I64, _I32, _I32, _P, _I32, _P]
@@ -264,12 +262,6 @@ def dora_decode_segment_pages(desc: dora_decode_desc) -> int:
     """Pages per workgroup where the decode runs per segment, 0 where it is stream-K
     (see include/dora_measure.h)."""
     return int(_lib.dora_decode_segment_pages(ctypes.byref(desc)))
-
-
-def dora_decode_grouped_as_plain(desc: dora_decode_desc) -> int:
-    """1 where a grouped decode that returns no shared page counts runs as the plain
-    one (see include/dora_measure.h)."""
-    return int(_lib.dora_decode_grouped_as_plain(ctypes.byref(desc)))
 
 
 # Workspaces the binding allocates when the caller passes none: one per

@@ -381,25 +381,3 @@ def test_segment_split_lines(d, dt, d_, P, B, Hkv, stride, tokens):
     assert d.dora_decode_segment_pages(d.make_decode_desc(**kw)) * P == tokens
     for cut in ({"num_waves": 100}, {"min_range_pages": 8}):
         assert d.dora_decode_segment_pages(d.make_decode_desc(**kw, **cut)) == 0
-
-
-@pytest.mark.parametrize("dt,d_,P,B,Hkv,stride,plain", [
-    (0, 128, 16, 16, 4, 256, 1),         # 256-token chunks
-    (1, 128, 16, 20, 16, 128, 1),        # 512-token chunks
-    (0, 128, 16, 512, 2, 32, 1),         # 1,024 whole segments of 512 tokens, 256 MiB
-    (0, 128, 16, 512, 2, 33, 0),         # past it
-    (0, 128, 16, 513, 2, 32, 0),         # past 1,024 segments
-    (1, 128, 16, 1024, 1, 64, 1),        # fp8: 1,024 tokens a row
-    (1, 128, 16, 1024, 1, 65, 0),
-    (0, 64, 32, 512, 2, 32, 1),
-    (0, 64, 32, 512, 2, 33, 0),
-    (0, 128, 16, 1024, 8, 64, 0),        # stream-K
-])
-def test_grouped_as_plain_lines(d, dt, d_, P, B, Hkv, stride, plain):
-    """A grouped call without counts runs as the plain decode where that is per
-    segment and the tables' rows fit the last-level cache; never where the caller
-    sets the cut."""
-    kw = dict(num_seqs=B, num_q_heads=4 * Hkv, num_kv_heads=Hkv, head_dim=d_, page_size=P,
-              block_table_stride=stride, num_pages=1000, kv_dtype=dt)
-    assert d.dora_decode_grouped_as_plain(d.make_decode_desc(**kw)) == plain
-    assert d.dora_decode_grouped_as_plain(d.make_decode_desc(**kw, num_waves=100)) == 0
