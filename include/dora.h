@@ -169,12 +169,13 @@ int64_t dora_decode_num_waves(const dora_decode_desc* desc);
  *                aligned; contents on entry are ignored
  * Launches the decode kernel and a log-sum-exp combine kernel on `stream` (per
  * 8192 sequences).  Every decode wavefront takes an equal share of the batch's
- * (page, KV head) work, whatever the length mix.  Batches whose block tables
- * are short (up to 1,024-2,048 tokens a row), or hold few (sequence, KV head)
- * segments, run one workgroup per segment, or per chunk of 256 or 512 tokens of
- * it, instead; the former is one launch.  Results do not depend on the
- * number of wavefronts beyond fp32 rounding, and repeated calls on the same
- * inputs and device are bitwise identical. */
+ * (page, KV head) work, whatever the length mix.  Batches with few (sequence, KV
+ * head) segments or short block tables run per segment instead, by lines on both
+ * and on the page geometry: one workgroup per segment, in one launch (rows of up to
+ * 512-2,048 tokens), or one per chunk of 256 or 512 tokens of it and a combine (rows
+ * from 768 tokens on); dora_decode_segment_pages in dora_measure.h tells which.
+ * Results do not depend on the number of wavefronts beyond fp32 rounding, and
+ * repeated calls on the same inputs and device are bitwise identical. */
 dora_status dora_decode_attn(const dora_decode_desc* desc,
                              const void* q, const void* k_pages, const void* v_pages,
                              const int32_t* block_table, const int32_t* seq_lens,

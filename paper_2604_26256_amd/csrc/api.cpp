@@ -116,11 +116,13 @@ int segment_split(const dora_decode_desc& d, int64_t segs, int64_t waves) {
 // runs as the plain decode: where that takes the segment kernel.  The members'
 // copies of a prompt then mostly come out of the caches, while the grouped call
 // adds detection, prefix partials and a suffix stream-K that cost 20-40 us
-// however little there is to do.  Grouped over plain, 5,000 random batches of
-// the lines above (2-16 members, prompts of 64-5,000 tokens, 64-2,048 tokens of
-// response at the median): 256-token chunks 2.2-2.9x (the worst 1.2x), 512-token
-// chunks 1.5-2.3x (0.95x), whole segments 1.4-4x up to 1,024 of them (0.99x);
-// beyond, 1.1-1.4x but 0.82x where the prompts are the bulk of the context.
+// however little there is to do.  Grouped over plain, 23,094 random batches that the
+// segment kernel takes (2-128 members, prompts of 16-16,384 tokens, 8-4,096 tokens of
+// response at the median): 256-token chunks 2.4x (the worst 1.00), 512-token chunks
+// 1.8x (11 of 3,776 below 0.97, the worst 0.90), whole segments up to 1,024 of them
+// 3.4x: 3.5x while the tables' rows fit the 256 MB last-level cache (none of 10,762
+// below 0.97), 1.4x past it (16 of 198, the worst 0.71); more than 1,024 segments run
+// grouped: 1.1-1.4x as plain, but 0.82x where the prompts are the bulk of the context.
 bool grouped_as_plain(const dora_decode_desc& d, int64_t waves) {
   const int64_t segs = (int64_t)d.num_seqs * d.num_kv_heads;
   if (segs > 2048) return false;

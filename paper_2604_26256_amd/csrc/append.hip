@@ -122,7 +122,7 @@ __device__ __forceinline__ u32x4 map_codes(u32x4 w, const uint8_t* lut, int live
 // scale s0 to s is the same for every code of the page, so its 256 results are
 // computed once and looked up; pages move in 16-byte pieces, kRequantBatch of
 // them in flight per thread (with it, appends that grow scales take no longer
-// than appends that don't: 107 and 106 us for the four calls above).
+// than appends that don't).
 constexpr int kRequantBatch = 4;
 template <bool IS_K>
 __device__ void requantise(uint8_t* __restrict__ page, const uint8_t* lut, int n, int P, int slot) {

@@ -39,9 +39,9 @@
 //   segment  small batches: one workgroup per segment, or per chunk of it, in
 //            place of stream-K (segment_kernel).
 //   combine  one workgroup per record: the log-sum-exp merge of the pieces
-//            of a cut segment.  The grouped decode's variant has one
-//            workgroup per segment and also folds every row with the
-//            partials of its group's shared prefix.
+//            of a cut segment.  The grouped decode's variant has one workgroup
+//            per segment, or four where it has many pieces, and also folds every
+//            row with the partials of its group's shared prefix.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -1,6 +1,6 @@
 // Decode attention of small batches: a workgroup per (sequence, KV head) segment,
 // or per chunk of it, in place of the stream-K decode (decode.hip), with the same
-// per-page step.
+// per-page step, and the combine of a segment's chunks.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -19,8 +19,8 @@ namespace dora {
 // chain before the first page is one memory round trip, since a wave's table
 // entries (lane u holds its u-th page) do not wait for the length.
 //   What bounds it: latency.  8 sequences, 2 KV heads of 64, 256 tokens at the
-// median (two launches before): 12.0 -> 6.0 us a call; 3 sequences of 6,000 fp8
-// tokens, 8 KV heads of 128: 22.6 -> 15.1 us.
+// median: 12.0 us by stream-K (two launches), 6.0 here (one); 3 sequences of 6,000
+// fp8 tokens, 8 KV heads of 128: 22.6 by stream-K, 15.4 here, with the combine.
 //   Two page buffers, four waves: a third buffer costs loads past the end that
 // short segments wait for, one is slower for long ones (8 segments of 24 / 96
 // pages of 16 bf16 tokens: 5.7 / 13.9 us with two; geometric mean over 700
